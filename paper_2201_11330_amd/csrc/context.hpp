@@ -94,6 +94,9 @@ struct lbm_ctx {
     // Rows per segment of the streamed D2Q9 launches (0: not planned yet).
     int stream_rows = 0;
 
+    // Planes per segment of the two-step 3D launches (0: not planned yet).
+    int march_planes = 0;
+
     // LBM_FLAG_GRAPH: kGraphSteps steps captured once, replayed by lbm_step.
     bool use_graph = false;
     hipStream_t capture_stream = nullptr;
@@ -164,11 +167,9 @@ inline StepArgs<C> step_args(const lbm_ctx* c)
     p.g = dims_of(c);
     p.bx_shift = c->bx_shift;
     p.xcd_rows = 0;  // launches on grid_xcd set it
-    p.c.omega = C(c->omega);
-    for (int d = 0; d < 3; ++d) p.c.F[d] = C(c->F[d]);
-    const double half = 1.0 - 0.5 * c->omega;
-    p.c.k3 = C(3.0 * half);
-    p.c.k9 = C(9.0 * half);
+    p.c = c->lattice == LBM_D2Q9    ? collide_args<0, C>(c->omega, c->F)
+          : c->lattice == LBM_D3Q19 ? collide_args<1, C>(c->omega, c->F)
+                                    : collide_args<2, C>(c->omega, c->F);
     return p;
 }
 

@@ -4,6 +4,7 @@
 
 #include "context.hpp"
 #include "fused2d.hpp"
+#include "march3d.hpp"
 #include "stream2d.hpp"
 
 namespace imexlbm {
@@ -193,9 +194,85 @@ struct Impl {
         }
     }
 
+    // Two steps per launch through the planes of a 3D box (march3d.hpp): FP64
+    // and FP32 storage.
+    static constexpr bool kMarch = L != 0 && (std::is_same_v<S, double> || std::is_same_v<S, float>);
+
+    static constexpr bool kMarchWallsToo = L == 1 || sizeof(S) == 8;
+
+    template <class K>
+    static void step_march(lbm_ctx* c, const S* src, S* dst)
+    {
+        if constexpr (!K::walls) step_march_of<K, kMarchOpen>(c, src, dst);
+        else if constexpr (!kMarchWallsToo) return;  // takes_march excludes it
+        else if (c->nodal >= 0) step_march_of<K, kMarchNodal>(c, src, dst);
+        else if (c->links) step_march_of<K, kMarchMask>(c, src, dst);
+        else step_march_of<K, kMarchAxes>(c, src, dst);
+    }
+    template <class K, int WK>
+    static void step_march_of(lbm_ctx* c, const S* src, S* dst)
+    {
+        constexpr int threads = kMarchThreads<L>, most_rows = kMarchRows<L>;
+        const auto kernel = k_step_ab_march<L, S, WK, K::force, K::comp>;
+        MarchMap m;
+        m.tiles_x = (c->nx + kMarchCols - 1) / kMarchCols;
+        m.tiles_y = (c->ny + most_rows - 1) / most_rows;
+        m.rows = (c->ny + m.tiles_y - 1) / m.tiles_y;
+        const long long cols = (long long)m.tiles_x * m.tiles_y;
+        if (c->march_planes == 0) {
+            int cus = 0;
+            if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess || cus < 1) {
+                (void)hipGetLastError();
+                cus = 256;
+            }
+            c->march_planes = march_planes(c->nz, cols, (long long)kMarchPerCu<S> * cus);
+        }
+        m.planes = c->march_planes;
+        m.total = int(cols * ((c->nz + m.planes - 1) / m.planes));
+        m.chunk = (m.total + 7) / 8;
+        hipLaunchKernelGGL(kernel, dim3(unsigned(m.chunk) * 8), dim3(threads), 0, c->stream, src, dst,
+                           step_args<S>(c), m);
+    }
+
+    // Whether the box takes the two-step launches: decided by measurement,
+    // one-step against two-step launches on boxes from 40^3 to 512^2 x 40.
+    //   * The lanes of a row are padded to 64 there and to a power of two or
+    //     a multiple of 256 in the one-step kernels; where the two-step
+    //     padding is larger (nx <= 32) it lost (x0.5-0.9).
+    //   * Small boxes leave CUs idle or make segments of a few planes, which
+    //     repeat level 1 of two more each.  FP64: x0.8-1.0 up to 56^3,
+    //     x1.02-1.17 from 64^3, x1.3 and more from 90^3; between walls
+    //     x0.8-1.0 below 2^19 nodes (D3Q27: 2^20) and x1.05-1.3 above.
+    //     FP32: x0.8-1.08 up to 128 x 64 x 64, x1.1-1.8 from 5 * 2^17 nodes;
+    //     between walls from 2^21 (x1.03-1.46), D3Q27 not at all.
+    //   * Boxes of fewer than 4 planes: 512 x 512 x 2 x0.89.
+    static bool takes_march(const lbm_ctx* c)
+    {
+        const unsigned lanes = unsigned((c->nx + 63) / 64) * 64, one_step = c->grid.x << c->bx_shift;
+        if (c->aa || lanes > one_step || c->nz < 4 || (unsigned long long)c->nx * c->ny > kMarchMaxPlane) return false;
+        if (sizeof(S) == 8) return c->N >= (!c->walls ? 1u << 18 : L == 1 ? 1u << 19 : 1u << 20);
+        return c->walls ? kMarchWallsToo && c->N >= 1u << 21 : c->N >= 5u << 17;
+    }
+
     static lbm_status eager(lbm_ctx* c, int n)
     {
         int i = 0;
+        if constexpr (kMarch) {
+            if (takes_march(c)) {
+                // In pairs of launches where graphs are captured, so that the
+                // current buffer keeps following the parity of the steps.
+                const int launches = c->use_graph ? 2 : 1;
+                for (; n - i >= 2 * launches; i += 2 * launches) {
+                    for (int h = 0; h < launches; ++h) {
+                        const S* src = static_cast<const S*>(c->buf[c->cur]);
+                        S* dst = static_cast<S*>(c->buf[1 - c->cur]);
+                        dispatch(c, [&](auto k) { step_march<decltype(k)>(c, src, dst); });
+                        c->cur = 1 - c->cur;
+                    }
+                    c->steps += 2 * launches;
+                }
+            }
+        }
         if constexpr (L == 0) {
             // Periodic D2Q9, two lattices: launches of kFuseSteps steps, in
             // pairs so that the current buffer keeps following the parity of

@@ -356,12 +356,39 @@ __device__ __forceinline__ S get(const S* p)
 // On deviations (DEV) sum g = rho - 1, and feq_a - w_a =
 // w_a (rho - 1 + rho (3 e_a.u + 4.5 (e_a.u)^2 - 1.5 u.u)).
 
+//
+// In FP64 the force term is added per pair of opposite directions (a, abar):
+// with G = 3 (1 - omega/2) w_a e_a.F, formed once on the host,
+//   f*_a += (3 e_a.u G - 3 (1 - omega/2) w_a u.F) + G,
+//   f*_abar += (3 e_a.u G - 3 (1 - omega/2) w_a u.F) - G,
+// six operations per pair; the term as it stands takes five per direction and
+// the sums e_a.F (two-step launches, march3d.hpp: D3Q19 channel 512 x 128 x
+// 128 280 -> 272 us per step).  FP32 arithmetic keeps the term as it stands:
+// there its rounding is seen in the results.
+
 template <class C>
 struct CollideArgs {
     C omega;
     C F[3];
-    C k3, k9;  // 3 (1 - omega/2), 9 (1 - omega/2)
+    C k3, k9;    // 3 (1 - omega/2), 9 (1 - omega/2)
+    C push[13];  // G of a = 0 .. Q/2 - 1
 };
+
+// The arguments of lattice L.
+template <int L, class C>
+CollideArgs<C> collide_args(double omega, const double (&F)[3])
+{
+    constexpr auto& LT = kLattice<L>;
+    CollideArgs<C> p{};
+    p.omega = C(omega);
+    for (int d = 0; d < 3; ++d) p.F[d] = C(F[d]);
+    const double half = 1.0 - 0.5 * omega;
+    p.k3 = C(3.0 * half);
+    p.k9 = C(9.0 * half);
+    for (int a = 0; a < Lattice<L>::Q / 2; ++a)
+        p.push[a] = C(3.0 * half * LT.w[a] * (LT.e[a][0] * F[0] + LT.e[a][1] * F[1] + LT.e[a][2] * F[2]));
+    return p;
+}
 
 template <int L, class C>
 struct Moments {
@@ -405,6 +432,7 @@ __device__ __forceinline__ Moments<L, C> node_moments(const C (&f)[Lattice<L>::Q
 template <int L, class C, bool FORCE, bool COMP = false, bool DEV = false>
 __device__ __forceinline__ void collide(C (&f)[Lattice<L>::Q], const CollideArgs<C>& p)
 {
+    constexpr bool kPairForce = std::is_same_v<C, double>;
     const Moments<L, C> m = node_moments<L, C, FORCE, COMP, DEV>(f, p.F);
     const C usq = m.ux * m.ux + m.uy * m.uy + (kDim<L> == 3 ? m.uz * m.uz : C(0));
     const C base = m.rho - C(1.5) * (COMP ? m.rf * usq : usq);
@@ -417,12 +445,23 @@ __device__ __forceinline__ void collide(C (&f)[Lattice<L>::Q], const CollideArgs
         const C edu = eterm<ex>(m.ux) + eterm<ey>(m.uy) + eterm<ez>(m.uz);
         const C feq = w * (base + (COMP ? m.rf * edu : edu) * (C(3) + C(4.5) * edu));
         C fs = f[a] + p.omega * (feq - f[a]);
-        if constexpr (FORCE) {
+        if constexpr (FORCE && !kPairForce) {
             const C eF = eterm<ex>(p.F[0]) + eterm<ey>(p.F[1]) + eterm<ez>(p.F[2]);
             fs += w * (p.k3 * (eF - uF) + p.k9 * edu * eF);
         }
         f[a] = fs;
     });
+    if constexpr (FORCE && kPairForce) {
+        static_for<Lattice<L>::Q / 2>([&](auto ac) {
+            constexpr int a = decltype(ac)::value, abar = Lattice<L>::opp(a);
+            constexpr int ex = kLattice<L>.e[a][0], ey = kLattice<L>.e[a][1], ez = kLattice<L>.e[a][2];
+            const C edu = eterm<ex>(m.ux) + eterm<ey>(m.uy) + eterm<ez>(m.uz);
+            const C both = C(3) * edu * p.push[a] - C(kLattice<L>.w[a]) * (p.k3 * uF);
+            f[a] += both + p.push[a];
+            f[abar] += both - p.push[a];
+        });
+        f[Lattice<L>::Q / 2] -= C(kLattice<L>.w[Lattice<L>::Q / 2]) * (p.k3 * uF);
+    }
 }
 
 // ---------------------------------------------------------------------------
