@@ -1,5 +1,5 @@
-// Several time steps of a fully periodic D2Q9 box in one launch (two-lattice
-// pattern, temporal blocking in LDS).
+// Several time steps of a D2Q9 box in one launch (two-lattice pattern,
+// temporal blocking in LDS).
 //
 // A 256-item workgroup holds an E x E region of nodes (E = 16: one node per
 // work-item; E = 32: four), loads the stored state of that region once and
@@ -11,7 +11,9 @@
 // stored; the ring around them is recomputed by the neighbouring workgroups,
 // which replaces a grid-wide barrier by redundant arithmetic.  Region nodes
 // take their coordinates modulo the box, so boxes smaller than a region wrap
-// the same way.  With a reduced-precision storage every step rounds its
+// the same way; across walls nothing pulls from such an image.  Where a pull
+// source is a wall (Eq. (bb)) a node takes its own opposite population, by
+// link bits formed or read once per launch.  With a reduced-precision storage every step rounds its
 // result through the storage type, as a store and reload would, so the state
 // after 4 steps is bit for bit that of 4 one-step launches.
 //
@@ -22,7 +24,9 @@
 // price of the ring's arithmetic: 4x the useful collisions with E = 16,
 // 1.78x with E = 32.  Measured on MI355X, FP64: 128^2 12,800-13,300 vs
 // 3,900-5,800 MLUPS (one step per launch); 4096^2 95,000 vs 42,900 MLUPS
-// (E = 32 vs the two-node one-step kernel).  4 steps per pass beat 2, 3, 5
+// (E = 32 vs the two-node one-step kernel).  Between walls, us per step
+// against one launch per step: 128^2 4.1 -> 1.8, 512 x 128 with a cylinder
+// 5.2 -> 2.6, 512^2 9.6 -> 5.4, 1000 x 777 22.1 -> 13.6.  4 steps per pass beat 2, 3, 5
 // and 6 on every box from 64^2 to 4096^2.
 #pragma once
 
@@ -98,9 +102,30 @@ inline FuseMap fuse_plan(int nx, int ny, int inner, int tile, dim3* grid)
     return m;
 }
 
-template <int E, class S, bool FORCE, bool COMP, bool NT>
+// Link bits of a node: bit a where the pull source x - e_a is a wall, bit 31
+// where the node is solid; from the mask where there is one, else what the
+// walls across x and those across y give.  Directions are a = 3 (e_x + 1) +
+// (e_y + 1).
+__device__ __forceinline__ unsigned axis_bits_2d(const Dims& g, int axis, int c)
+{
+    const int n = axis == 0 ? g.nx : g.ny;
+    const Axis3 w = axis3<true>(c, n, g.bc[axis]);
+    const unsigned minus = axis == 0 ? 0x007u : 0x049u;  // directions with e = -1, 0, +1
+    const unsigned zero = axis == 0 ? 0x038u : 0x092u, plus = axis == 0 ? 0x1C0u : 0x124u;
+    return (w.wall[0] ? plus : 0u) | (w.wall[1] ? zero : 0u) | (w.wall[2] ? minus : 0u) |
+           (g.bc[axis] == kSolidEnds && (c == 0 || c == n - 1) ? 1u << 31 : 0u);
+}
+
+__device__ __forceinline__ unsigned link_bits_2d(const Dims& g, int x, int y)
+{
+    if (g.links) return g.links[node_index(g, x, y, 0)];
+    return axis_bits_2d(g, 0, x) | axis_bits_2d(g, 1, y);
+}
+
+// `steps` (1 .. kFuseSteps) is the number of steps of this launch.
+template <int E, class S, bool WALLS, bool FORCE, bool COMP, bool NT>
 __global__ __launch_bounds__(256) void k_step_ab_fused2d(const S* __restrict__ src, S* __restrict__ dst,
-                                                         StepArgs<typename Store<S>::C> p, FuseMap m)
+                                                         StepArgs<typename Store<S>::C> p, FuseMap m, int steps)
 {
     using C = typename Store<S>::C;
     constexpr int L = 0, Q = Lattice<L>::Q, H = kFuseSteps, I = kFuseInnerOf<E>;
@@ -113,6 +138,7 @@ __global__ __launch_bounds__(256) void k_step_ab_fused2d(const S* __restrict__ s
     const int tx = int(threadIdx.x) & 15, ty = int(threadIdx.x) >> 4;
     const int TS = g.S;
     C f[NPT][Q];
+    unsigned bits[NPT];
 #pragma unroll
     for (int j = 0; j < NPT; ++j) {
         const int lx = tx + 16 * (j % NE), ly = ty + 16 * (j / NE);
@@ -125,8 +151,9 @@ __global__ __launch_bounds__(256) void k_step_ab_fused2d(const S* __restrict__ s
             constexpr int a = decltype(ac)::value;
             f[j][a] = Store<S>::load(src[slot<Q>(a, node, TS)]);
         });
+        bits[j] = WALLS ? link_bits_2d(g, gx, gy) : 0u;
     }
-    for (int s = 0; s < H; ++s) {
+    for (int s = 0; s < steps; ++s) {
 #pragma unroll
         for (int j = 0; j < NPT; ++j) {
             const int lx = tx + 16 * (j % NE), ly = ty + 16 * (j / NE);
@@ -150,11 +177,20 @@ __global__ __launch_bounds__(256) void k_step_ab_fused2d(const S* __restrict__ s
                 if constexpr (ey == 1) sy = sy < 0 ? 0 : sy;
                 if constexpr (ey == -1) sy = sy > E - 1 ? E - 1 : sy;
                 f[j][a] = sh[a][sy][sx];
+                if constexpr (WALLS) {  // from a wall: the node's own opposite population
+                    if ((bits[j] >> a) & 1u) f[j][a] = sh[Lattice<L>::opp(a)][ly][lx];
+                }
             });
         }
         __syncthreads();
 #pragma unroll
         for (int j = 0; j < NPT; ++j) {
+            if constexpr (WALLS) {
+                if (g.nodal >= 0) {
+                    const int lx = tx + 16 * (j % NE), ly = ty + 16 * (j / NE);
+                    nodal_fill<L>(g, wrap_into(bx * I - H + lx, g.nx), wrap_into(by * I - H + ly, g.ny), 0, f[j]);
+                }
+            }
             collide<L, C, FORCE, COMP, Store<S>::kDeviation>(f[j], p.c);
             if constexpr (!std::is_same_v<S, C>) {
                 static_for<Q>([&](auto ac) {
@@ -171,6 +207,7 @@ __global__ __launch_bounds__(256) void k_step_ab_fused2d(const S* __restrict__ s
         if (ix < 0 || ix >= I || iy < 0 || iy >= I) continue;
         const int ox = bx * I + ix, oy = by * I + iy;
         if (ox >= g.nx || oy >= g.ny) continue;
+        if (WALLS && (bits[j] >> 31)) continue;
         const unsigned own = unsigned(ox) + unsigned(g.nx) * unsigned(oy);
         // Non-temporal global stores: the nt | sc1 buffer stores of the
         // one-step kernels measured slower here (128^2: 11,950 vs 12,500-

@@ -152,11 +152,12 @@ struct Impl {
         return eager(c, n);
     }
 
-    // kFuseSteps steps of a periodic D2Q9 two-lattice box in one launch:
-    // 32 x 32 regions on large boxes, 16 x 16 regions otherwise (XCD-aware
-    // placement from kFuseXcdMinBlocks blocks up); see fused2d.hpp.
+    // `steps` (2 .. kFuseSteps) steps of a D2Q9 two-lattice box in one
+    // launch: strips on the largest boxes, 32 x 32 regions on large
+    // boxes, 16 x 16 regions otherwise (XCD-aware placement from
+    // kFuseXcdMinBlocks blocks up); see stream2d.hpp and fused2d.hpp.
     template <class K>
-    static void step_fused2d(lbm_ctx* c, const S* src, S* dst)
+    static void step_fused2d(lbm_ctx* c, const S* src, S* dst, int steps)
     {
         constexpr int I32 = kFuseInnerOf<32>, I16 = kFuseInnerOf<16>;
         const auto blocks = [&](int inner) {
@@ -164,10 +165,10 @@ struct Impl {
         };
         const auto args = step_args<typename Store<S>::C>(c);
         dim3 grid;
-        if (c->N >= kStreamMinNodes) {
+        if (steps == kFuseSteps && c->N >= (K::walls ? kStreamMinNodesWalls : kStreamMinNodes)) {
             // Strips of kStreamStore stored columns, segments of rows chosen
             // once per context from the kernel's occupancy (stream_rows).
-            const auto kernel = k_step_ab_stream2d<S, K::force, K::comp, kNtStores>;
+            const auto kernel = k_step_ab_stream2d<S, K::walls, K::force, K::comp, kNtStores>;
             if (c->stream_rows == 0) {
                 int per_cu = 0, cus = 0;
                 if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, 256, 0) != hipSuccess ||
@@ -184,13 +185,13 @@ struct Impl {
             hipLaunchKernelGGL(kernel, grid, c->block, 0, c->stream, src, dst, args, rows);
         } else if (blocks(I32) >= kFuseBigMinBlocks) {
             const FuseMap m = fuse_plan(c->nx, c->ny, I32, 0, &grid);
-            hipLaunchKernelGGL((k_step_ab_fused2d<32, S, K::force, K::comp, kNtStores>), grid, c->block, 0,
-                               c->stream, src, dst, args, m);
+            hipLaunchKernelGGL((k_step_ab_fused2d<32, S, K::walls, K::force, K::comp, kNtStores>), grid, c->block, 0,
+                               c->stream, src, dst, args, m, steps);
         } else {
             const FuseMap m =
                 fuse_plan(c->nx, c->ny, I16, blocks(I16) >= kFuseXcdMinBlocks ? kFuseXcdTile : 0, &grid);
-            hipLaunchKernelGGL((k_step_ab_fused2d<16, S, K::force, K::comp, kNtStores>), grid, c->block, 0,
-                               c->stream, src, dst, args, m);
+            hipLaunchKernelGGL((k_step_ab_fused2d<16, S, K::walls, K::force, K::comp, kNtStores>), grid, c->block, 0,
+                               c->stream, src, dst, args, m, steps);
         }
     }
 
@@ -274,18 +275,30 @@ struct Impl {
             }
         }
         if constexpr (L == 0) {
-            // Periodic D2Q9, two lattices: launches of kFuseSteps steps, in
-            // pairs so that the current buffer keeps following the parity of
-            // the step count; the remainder runs one step per launch.
-            if (!c->aa && !c->walls) {
-                for (; n - i >= 2 * kFuseSteps; i += 2 * kFuseSteps) {
-                    for (int h = 0; h < 2; ++h) {
-                        const S* src = static_cast<const S*>(c->buf[c->cur]);
-                        S* dst = static_cast<S*>(c->buf[1 - c->cur]);
-                        dispatch(c, [&](auto k) { step_fused2d<decltype(k)>(c, src, dst); });
-                        c->cur = 1 - c->cur;
+            // D2Q9, two lattices: launches of up to kFuseSteps steps.  Where
+            // graphs are captured, in pairs of kFuseSteps steps, so that the
+            // current buffer keeps following the parity of the step count,
+            // and the remainder one step per launch; a last single step is
+            // always a one-step launch.  Large boxes in 16-bit storage between
+            // walls on the axes are left to the one-step kernel (2048^2 FP16:
+            // 32.8 us per step, strips 34.8 with halfway and 38.6 with nodal
+            // walls; with a mask 40.3 and 33.8).
+            if (!c->aa && !(sizeof(S) == 2 && c->walls && !c->links && c->N >= kStreamMinNodesWalls)) {
+                const auto fuse = [&](int steps) {
+                    const S* src = static_cast<const S*>(c->buf[c->cur]);
+                    S* dst = static_cast<S*>(c->buf[1 - c->cur]);
+                    dispatch(c, [&](auto k) { step_fused2d<decltype(k)>(c, src, dst, steps); });
+                    c->cur = 1 - c->cur;
+                    c->steps += steps;
+                    i += steps;
+                };
+                if (c->use_graph) {
+                    while (n - i >= 2 * kFuseSteps) {
+                        fuse(kFuseSteps);
+                        fuse(kFuseSteps);
                     }
-                    c->steps += 2 * kFuseSteps;
+                } else {
+                    while (n - i >= 2) fuse(n - i < kFuseSteps ? n - i : kFuseSteps);
                 }
             }
         }

@@ -143,6 +143,13 @@ __device__ __forceinline__ unsigned node_index(const Dims& g, int x, int y, int 
     return unsigned(x) + unsigned(g.nx) * (unsigned(y) + unsigned(g.ny) * unsigned(z));
 }
 
+// Coordinate c modulo n.
+__device__ __forceinline__ int wrap_into(int c, int n)
+{
+    c %= n;
+    return c < 0 ? c + n : c;
+}
+
 // Element offset of direction a of node idx in a stored state.
 template <int Q>
 __device__ __forceinline__ size_t slot(int a, unsigned idx, int S)

@@ -124,12 +124,6 @@ struct MarchDirs {
     }
 };
 
-__device__ __forceinline__ int wrap_into(int c, int n)
-{
-    c %= n;
-    return c < 0 ? c + n : c;
-}
-
 // Buffer resource over `bytes` bytes from p (accesses past them read 0 and
 // write nothing), and loads and stores through it at byte offset voff (per
 // lane) + soff (wave-uniform).

@@ -1,4 +1,4 @@
-// Four time steps of a large periodic D2Q9 box in one pass over the state
+// Four time steps of a large D2Q9 box in one pass over the state
 // (two-lattice pattern), streaming up the rows of a strip of columns.
 //
 // A 256-item workgroup owns a strip of 256 columns (one per work-item: the
@@ -23,13 +23,18 @@
 // Against the regions of fused2d.hpp (32 x 32 nodes around 24 x 24 stored
 // ones), a launch fetches the state 1.14 x (256 of 224 columns) x
 // (rows + 8) / rows instead of ~2.7 x, writes whole lines, and repeats
-// that fraction of the collisions instead of 1.78 x.  The arithmetic per
+// that fraction of the collisions instead of 1.78 x.  Where a pull source
+// is a wall (Eq. (bb)), the node's own opposite population takes its place:
+// for e_y = 0 and +1 when the node's row is new, for e_y = -1 from the
+// node's own e_y = +1 populations, kept for one more row.  Columns and rows
+// past the box are images of its other end; across walls nothing pulls from
+// them.  The arithmetic per
 // node and step is that of the one-step kernels, in the same order, so the
 // state after 4 steps is bit for bit that of 4 one-step launches (each
 // level rounds through the storage type, as a store and reload would).
 #pragma once
 
-#include "kernels.hpp"
+#include "fused2d.hpp"
 
 namespace imexlbm {
 
@@ -40,6 +45,10 @@ constexpr int kStreamLevels = 4;  // steps per launch
 // Boxes of at least kStreamMinNodes nodes take these launches (smaller ones
 // the regions of fused2d.hpp).
 constexpr unsigned kStreamMinNodes = 1u << 20;
+// Between walls (FP64: 196 registers instead of 138, two wavefronts per SIMD
+// instead of three) from twice as many: 1024^2 17.3 us per step, regions
+// 16.8; 2048^2 47.0, regions 56.7, the one-step kernel 95.4.
+constexpr unsigned kStreamMinNodesWalls = 1u << 21;
 
 // Rows per segment for an nx x ny box when the GPU runs `slots` workgroups
 // of the kernel at once.  Every workgroup runs rows + 2 H iterations, so a
@@ -87,7 +96,7 @@ __device__ __forceinline__ C lane_shift(C v)
 // D2Q9 directions are a = 3 (e_x + 1) + (e_y + 1): a = 0, 1, 2 have
 // e_x = -1, a = 6, 7, 8 e_x = +1; a = 0, 3, 6 have e_y = -1, a = 2, 5, 8
 // e_y = +1.
-template <class S, bool FORCE, bool COMP, bool NT>
+template <class S, bool WALLS, bool FORCE, bool COMP, bool NT>
 __global__ __launch_bounds__(256) void k_step_ab_stream2d(const S* __restrict__ src, S* __restrict__ dst,
                                                           StepArgs<typename Store<S>::C> p, int rows)
 {
@@ -114,23 +123,48 @@ __global__ __launch_bounds__(256) void k_step_ab_stream2d(const S* __restrict__ 
 #pragma unroll
         for (int i = 0; i < 3; ++i) d0[k][i] = d1[k][i] = d2[k][i] = C(0);
     C nxt[Q];
+    // Walls: the node's own e_y = +1 of row r (what a wall above returns),
+    // and the link bits of the rows in flight: at[k] of the new row of level
+    // k, at[k + 1] of the row that level k + 1 collides.
+    C back[H][3];
+    unsigned at[H + 1], bits_x = 0;
+    if constexpr (WALLS) {
+        bits_x = axis_bits_2d(g, 0, gx);
+#pragma unroll
+        for (int k = 0; k < H; ++k)
+#pragma unroll
+            for (int i = 0; i < 3; ++i) back[k][i] = C(0);
+#pragma unroll
+        for (int k = 0; k <= H; ++k) at[k] = 0u;
+    }
+    const auto row_of = [&](int j) { return wrap_into(y0 - H + j, g.ny); };
 
     const auto load_row = [&](int j, C (&out)[Q]) {
-        int gy = (y0 - H + j) % g.ny;
-        gy += gy < 0 ? g.ny : 0;
-        const unsigned node = unsigned(gx) + unsigned(g.nx) * unsigned(gy);
+        const unsigned node = unsigned(gx) + unsigned(g.nx) * unsigned(row_of(j));
         static_for<Q>([&](auto ac) {
             constexpr int a = decltype(ac)::value;
             out[a] = Store<S>::load(src[slot<Q>(a, node, TS)]);
         });
     };
 
+    const auto bits_of = [&](int j) -> unsigned {
+        const int y = row_of(j);
+        return g.links ? g.links[node_index(g, gx, y, 0)] : bits_x | axis_bits_2d(g, 1, y);
+    };
+
     const int iters = nrows + 2 * H;
     load_row(0, nxt);
+    unsigned ahead = WALLS ? bits_of(0) : 0u;  // read a row ahead of their use
     for (int j = 0; j < iters; ++j) {
         C v[Q];
 #pragma unroll
         for (int a = 0; a < Q; ++a) v[a] = nxt[a];
+        if constexpr (WALLS) {
+#pragma unroll
+            for (int k = H; k > 0; --k) at[k] = at[k - 1];
+            at[0] = ahead;
+            ahead = bits_of(j + 1);
+        }
         if (j + 1 < iters) load_row(j + 1, nxt);
 #pragma unroll
         for (int k = 0; k < H; ++k) {
@@ -174,7 +208,20 @@ __global__ __launch_bounds__(256) void k_step_ab_stream2d(const S* __restrict__ 
                 d2[k][i] = d1[k][i];
                 d1[k][i] = A[3 * i + 2];
                 d0[k][i] = A[3 * i + 1];
+                if constexpr (WALLS) {
+                    // From a wall: the node's own opposite population, of the
+                    // row collided now (e_y = -1) or of the new row, for when
+                    // that is collided (e_y = 0 and +1).
+                    if ((at[k + 1] >> (3 * i)) & 1u) f[3 * i] = back[k][2 - i];
+                    if ((at[k] >> (3 * i + 1)) & 1u) d0[k][i] = v[Q - 1 - (3 * i + 1)];
+                    if ((at[k] >> (3 * i + 2)) & 1u) d2[k][i] = v[Q - 1 - (3 * i + 2)];
+                }
             });
+            if constexpr (WALLS) {
+#pragma unroll
+                for (int i = 0; i < 3; ++i) back[k][i] = v[3 * i + 2];
+                if (g.nodal >= 0) nodal_fill<L>(g, gx, row_of(j - k - 1), 0, f);
+            }
             if (j >= 2 * (k + 1)) {  // uniform: the rows it pulls from exist
                 collide<L, C, FORCE, COMP, Store<S>::kDeviation>(f, p.c);
                 if constexpr (!std::is_same_v<S, C>) {
@@ -187,7 +234,7 @@ __global__ __launch_bounds__(256) void k_step_ab_stream2d(const S* __restrict__ 
 #pragma unroll
             for (int a = 0; a < Q; ++a) v[a] = f[a];
         }
-        if (j >= 2 * H && store_col) {
+        if (j >= 2 * H && store_col && !(WALLS && (at[H] >> 31))) {
             const unsigned own = unsigned(ox) + unsigned(g.nx) * unsigned(y0 + j - 2 * H);
             static_for<Q>([&](auto ac) {
                 constexpr int a = decltype(ac)::value;
