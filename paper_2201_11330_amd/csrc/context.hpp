@@ -113,11 +113,11 @@ struct Ops {
                          const double* noise);
     lbm_status (*export_f)(lbm_ctx*, double* f);
     lbm_status (*moments)(lbm_ctx*, void* rho, void* u, int f32);
-    lbm_status (*reduce)(lbm_ctx*, double* partials);  // partials: 5 kReduceBlocks + 4 doubles
+    lbm_status (*reduce)(lbm_ctx*, double* partials, double* out);  // partials: 5 kReduceBlocks doubles
     lbm_status (*adjoint)(lbm_ctx*, int n, int k, const void* ckpt, void* ws, const double* rho0,
                           const double* u0, const double* ubar, double* u0bar, double* out4);
     lbm_status (*build_links)(lbm_ctx*, const unsigned char* mask);
-    lbm_status (*wall_force)(lbm_ctx*);
+    lbm_status (*wall_force)(lbm_ctx*, double* out);
     lbm_status (*step_between)(lbm_ctx*, const void* src, void* dst);
 };
 

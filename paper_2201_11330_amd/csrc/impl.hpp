@@ -425,17 +425,20 @@ struct Impl {
         return LBM_OK;
     }
 
-    static lbm_status wall_force(lbm_ctx* c)
+    // out: 3 doubles, device memory or pinned host memory.
+    static lbm_status wall_force(lbm_ctx* c, double* out)
     {
         IoArgs p = io_args(c);
         const S* A = static_cast<const S*>(c->buf[c->cur]);
         hipLaunchKernelGGL((k_wall_force<L, S>), dim3(kReduceBlocks), dim3(kReduceThreads), 0, c->stream,
                            A, c->d_partials, p);
-        hipLaunchKernelGGL(k_sum3, dim3(1), dim3(kReduceThreads), 0, c->stream, c->d_partials,
-                           kReduceBlocks, c->d_partials + 5 * size_t(kReduceBlocks));
+        hipLaunchKernelGGL(k_sum3, dim3(1), dim3(kReduceThreads), 0, c->stream, c->d_partials, kReduceBlocks, out);
         LBM_HIP(hipGetLastError());
         return LBM_OK;
     }
+
+    // Work-items in node order (node_in_order).
+    static dim3 io_grid(const lbm_ctx* c) { return dim3(c->N / 256 + (c->N % 256 != 0)); }
 
     static lbm_status import(lbm_ctx* c, const double* f, const double* rho, const double* u,
                              const double* noise)
@@ -443,10 +446,10 @@ struct Impl {
         IoArgs p = io_args(c);
         S* A = static_cast<S*>(c->buf[c->cur]);
         if (c->walls)
-            hipLaunchKernelGGL((k_import<L, S, true>), c->grid, c->block, 0, c->stream, A, f, rho, u,
+            hipLaunchKernelGGL((k_import<L, S, true>), io_grid(c), c->block, 0, c->stream, A, f, rho, u,
                                noise, p);
         else
-            hipLaunchKernelGGL((k_import<L, S, false>), c->grid, c->block, 0, c->stream, A, f, rho, u,
+            hipLaunchKernelGGL((k_import<L, S, false>), io_grid(c), c->block, 0, c->stream, A, f, rho, u,
                                noise, p);
         LBM_HIP(hipGetLastError());
         return LBM_OK;
@@ -457,24 +460,31 @@ struct Impl {
         IoArgs p = io_args(c);
         const S* A = static_cast<const S*>(c->buf[c->cur]);
         if (c->walls)
-            hipLaunchKernelGGL((k_export<L, S, true>), c->grid, c->block, 0, c->stream, A, f, p);
+            hipLaunchKernelGGL((k_export<L, S, true>), io_grid(c), c->block, 0, c->stream, A, f, p);
         else
-            hipLaunchKernelGGL((k_export<L, S, false>), c->grid, c->block, 0, c->stream, A, f, p);
+            hipLaunchKernelGGL((k_export<L, S, false>), io_grid(c), c->block, 0, c->stream, A, f, p);
         LBM_HIP(hipGetLastError());
         return LBM_OK;
     }
 
-    template <class O>
+    template <class O, bool NT>
     static void moments_t(lbm_ctx* c, O* rho, O* u)
     {
         IoArgs p = io_args(c);
         const S* A = static_cast<const S*>(c->buf[c->cur]);
         if (c->walls)
-            hipLaunchKernelGGL((k_moments<L, S, true, O>), c->grid, c->block, 0, c->stream, A, rho, u,
-                               p);
+            hipLaunchKernelGGL((k_moments<L, S, true, O, NT>), io_grid(c), c->block, 0, c->stream, A, rho, u, p);
         else
-            hipLaunchKernelGGL((k_moments<L, S, false, O>), c->grid, c->block, 0, c->stream, A, rho,
-                               u, p);
+            hipLaunchKernelGGL((k_moments<L, S, false, O, NT>), io_grid(c), c->block, 0, c->stream, A, rho, u, p);
+    }
+    // Fields of more than 64 MiB are streamed: 512^3 FP16 with FP32 fields
+    // 1,290 -> 1,160 us, 256^3 FP64 570 -> 500; the 40 MiB of 193 x 127 x 101
+    // nodes in FP32 took 48 instead of 42 us that way.
+    template <class O>
+    static void moments_t(lbm_ctx* c, O* rho, O* u)
+    {
+        if (size_t(c->N) * 4 * sizeof(O) > (size_t(64) << 20)) moments_t<O, true>(c, rho, u);
+        else moments_t<O, false>(c, rho, u);
     }
 
     static lbm_status moments(lbm_ctx* c, void* rho, void* u, int f32)
@@ -487,9 +497,10 @@ struct Impl {
         return LBM_OK;
     }
 
-    // Monitor reduction into partials (5 kReduceBlocks + 4 doubles; the last
-    // four receive mass, kinetic energy, max |u| and the non-finite count).
-    static lbm_status reduce(lbm_ctx* c, double* partials)
+    // Monitor reduction by way of partials (5 kReduceBlocks doubles) into out
+    // (mass, kinetic energy, max |u| and the non-finite count; device memory
+    // or pinned host memory).
+    static lbm_status reduce(lbm_ctx* c, double* partials, double* out)
     {
         IoArgs p = io_args(c);
         const S* A = static_cast<const S*>(c->buf[c->cur]);
@@ -500,8 +511,7 @@ struct Impl {
             hipLaunchKernelGGL((k_reduce_partials<L, S, false>), dim3(kReduceBlocks),
                                dim3(kReduceThreads), 0, c->stream, A, partials, p);
         hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(kReduceThreads), 0, c->stream, partials,
-                           kReduceBlocks, int(Store<S>::kDeviation),
-                           partials + 5 * size_t(kReduceBlocks));
+                           kReduceBlocks, int(Store<S>::kDeviation), out);
         LBM_HIP(hipGetLastError());
         return LBM_OK;
     }
