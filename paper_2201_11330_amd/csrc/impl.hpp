@@ -10,8 +10,7 @@
 namespace imexlbm {
 
 // A captured run holds whole pairs of fused launches (see eager()).
-static_assert(kGraphSteps % (2 * kFuseSteps) == 0, "graph length must be a multiple of 2 * kFuseSteps");
-static_assert(kStreamLevels == kFuseSteps, "both multi-step launches take the same number of steps");
+static_assert(kGraphSteps % (2 * kFuseSteps) == 0 && kGraphSteps % 16 == 0, "a captured run holds whole pairs of launches");
 
 // Compile-time configuration of the step kernels: walls or masks present,
 // body force, compressible equilibrium (which always takes the force path).
@@ -152,10 +151,36 @@ struct Impl {
         return eager(c, n);
     }
 
-    // `steps` (2 .. kFuseSteps) steps of a D2Q9 two-lattice box in one
-    // launch: strips on the largest boxes, 32 x 32 regions on large
-    // boxes, 16 x 16 regions otherwise (XCD-aware placement from
-    // kFuseXcdMinBlocks blocks up); see stream2d.hpp and fused2d.hpp.
+    // Steps per launch of the strips of a D2Q9 box (0: it does not take them).
+    static int strip_levels(const lbm_ctx* c) { return stream_levels(c->N, sizeof(S), c->walls); }
+
+    // Strips of kStreamStore stored columns, segments of rows chosen once per
+    // context from the kernel's occupancy (stream_rows).
+    template <class K, int H>
+    static void step_strips(lbm_ctx* c, const S* src, S* dst)
+    {
+        const auto kernel = k_step_ab_stream2d<H, S, K::walls, K::force, K::comp, kNtStores>;
+        if (c->stream_rows == 0) {
+            int per_cu = 0, cus = 0;
+            if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, 256, 0) != hipSuccess ||
+                hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess ||
+                per_cu < 1 || cus < 1) {
+                (void)hipGetLastError();
+                per_cu = 4;  // unknown: assume a GPU of 256 CUs, 4 workgroups each
+                cus = 256;
+            }
+            c->stream_rows = stream_rows(c->nx, c->ny, (long long)per_cu * cus, H);
+        }
+        const int rows = c->stream_rows;
+        const dim3 grid(unsigned((c->nx + kStreamStore - 1) / kStreamStore), unsigned((c->ny + rows - 1) / rows), 1);
+        hipLaunchKernelGGL(kernel, grid, c->block, 0, c->stream, src, dst, step_args<typename Store<S>::C>(c), rows);
+    }
+
+    // `steps` (2 .. kFuseSteps, or strip_levels) steps of a D2Q9 two-lattice
+    // box in one launch: strips on the largest boxes, else (and for fewer
+    // steps) 32 x 32 regions on large boxes and 16 x 16 regions otherwise
+    // (XCD-aware placement from kFuseXcdMinBlocks blocks up); see
+    // stream2d.hpp and fused2d.hpp.
     template <class K>
     static void step_fused2d(lbm_ctx* c, const S* src, S* dst, int steps)
     {
@@ -165,24 +190,12 @@ struct Impl {
         };
         const auto args = step_args<typename Store<S>::C>(c);
         dim3 grid;
-        if (steps == kFuseSteps && c->N >= (K::walls ? kStreamMinNodesWalls : kStreamMinNodes)) {
-            // Strips of kStreamStore stored columns, segments of rows chosen
-            // once per context from the kernel's occupancy (stream_rows).
-            const auto kernel = k_step_ab_stream2d<S, K::walls, K::force, K::comp, kNtStores>;
-            if (c->stream_rows == 0) {
-                int per_cu = 0, cus = 0;
-                if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, 256, 0) != hipSuccess ||
-                    hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess ||
-                    per_cu < 1 || cus < 1) {
-                    (void)hipGetLastError();
-                    per_cu = 4;  // unknown: assume a GPU of 256 CUs, 4 workgroups each
-                    cus = 256;
-                }
-                c->stream_rows = stream_rows(c->nx, c->ny, (long long)per_cu * cus);
+        if (steps == strip_levels(c)) {
+            if (steps == 8) {
+                if constexpr (!K::walls && sizeof(S) > 2) step_strips<K, 8>(c, src, dst);
+            } else {
+                step_strips<K, 4>(c, src, dst);
             }
-            const int rows = c->stream_rows;
-            grid = dim3(unsigned((c->nx + kStreamStore - 1) / kStreamStore), unsigned((c->ny + rows - 1) / rows), 1);
-            hipLaunchKernelGGL(kernel, grid, c->block, 0, c->stream, src, dst, args, rows);
         } else if (blocks(I32) >= kFuseBigMinBlocks) {
             const FuseMap m = fuse_plan(c->nx, c->ny, I32, 0, &grid);
             hipLaunchKernelGGL((k_step_ab_fused2d<32, S, K::walls, K::force, K::comp, kNtStores>), grid, c->block, 0,
@@ -292,12 +305,16 @@ struct Impl {
                     c->steps += steps;
                     i += steps;
                 };
-                if (c->use_graph) {
-                    while (n - i >= 2 * kFuseSteps) {
-                        fuse(kFuseSteps);
-                        fuse(kFuseSteps);
+                const int most = strip_levels(c) ? strip_levels(c) : kFuseSteps;
+                for (int k = most;; k = kFuseSteps) {
+                    while (n - i >= 2 * k) {
+                        fuse(k);
+                        fuse(k);
                     }
-                } else {
+                    if (k == kFuseSteps || !c->use_graph) break;
+                }
+                if (!c->use_graph) {
+                    if (n - i >= most) fuse(most);
                     while (n - i >= 2) fuse(n - i < kFuseSteps ? n - i : kFuseSteps);
                 }
             }

@@ -1,11 +1,11 @@
-// Four time steps of a large D2Q9 box in one pass over the state
+// Four or eight (H) time steps of a large D2Q9 box in one pass over the state
 // (two-lattice pattern), streaming up the rows of a strip of columns.
 //
 // A 256-item workgroup owns a strip of 256 columns (one per work-item: the
 // kStreamStore = 224 columns it stores and 16 more on each side) and a
 // segment of rows.  It walks up the rows once: in iteration j it loads
 // stored row j (the post-collision state of the previous launch, "level
-// 0"), and each level k = 1..4 pulls (Eq. (propagation)) and collides (Eq.
+// 0"), and each level k = 1..H pulls (Eq. (propagation)) and collides (Eq.
 // (collision), the collide() of the one-step kernels) one row, lagging
 // level k - 1 by one row, so that the three rows it pulls from (e_y = +1,
 // 0, -1) have just been produced.  Per level a work-item keeps only what
@@ -13,16 +13,16 @@
 // e_y = +1 populations of two rows, already moved along x (Eq.
 // (propagation) in x: a wave shift between lanes, and between the
 // wavefronts of the workgroup through LDS, one barrier per level and row).
-// Level 4's rows are stored.  The two outermost columns lose one valid
-// column per level, so 4 columns on each side would cover the 4 levels;
+// Level H's rows are stored.  The two outermost columns lose one valid
+// column per level, so H columns on each side would cover the levels;
 // with 16 the strip starts on a 128-byte line and each wavefront stores
 // whole lines (with 8, whose 240 stored columns also start on a line, the
 // wavefronts split lines between them: 4096^2 FP64 ran 2 % slower).  A
-// segment re-reads 4 rows below and above its stored rows.
+// segment re-reads H rows below and above its stored rows.
 //
 // Against the regions of fused2d.hpp (32 x 32 nodes around 24 x 24 stored
 // ones), a launch fetches the state 1.14 x (256 of 224 columns) x
-// (rows + 8) / rows instead of ~2.7 x, writes whole lines, and repeats
+// (rows + 2 H) / rows instead of ~2.7 x, writes whole lines, and repeats
 // that fraction of the collisions instead of 1.78 x.  Where a pull source
 // is a wall (Eq. (bb)), the node's own opposite population takes its place:
 // for e_y = 0 and +1 when the node's row is new, for e_y = -1 from the
@@ -30,7 +30,7 @@
 // past the box are images of its other end; across walls nothing pulls from
 // them.  The arithmetic per
 // node and step is that of the one-step kernels, in the same order, so the
-// state after 4 steps is bit for bit that of 4 one-step launches (each
+// state after H steps is bit for bit that of H one-step launches (each
 // level rounds through the storage type, as a store and reload would).
 #pragma once
 
@@ -41,7 +41,6 @@ namespace imexlbm {
 constexpr int kStreamCols = 256;  // columns per workgroup, one per work-item
 constexpr int kStreamHalo = 16;   // loaded columns on each side of the stored ones
 constexpr int kStreamStore = kStreamCols - 2 * kStreamHalo;  // 224 stored columns
-constexpr int kStreamLevels = 4;  // steps per launch
 // Boxes of at least kStreamMinNodes nodes take these launches (smaller ones
 // the regions of fused2d.hpp).
 constexpr unsigned kStreamMinNodes = 1u << 20;
@@ -50,23 +49,37 @@ constexpr unsigned kStreamMinNodes = 1u << 20;
 // 16.8; 2048^2 47.0, regions 56.7, the one-step kernel 95.4.
 constexpr unsigned kStreamMinNodesWalls = 1u << 21;
 
+// Steps per launch of a box (0: it does not take strips).  Eight steps read
+// and write the state half as often as four, but hold twice the registers
+// (FP64: 234 instead of 138, two wavefronts per SIMD instead of three) and
+// repeat 16 rows per segment instead of 8.  us per step, four against eight:
+// FP64 1500 x 1100 17.7 / 18.0, 2048^2 35.2 / 32.9, 4096^2 120.9 / 101.9;
+// FP32 2048^2 20.0 / 19.8, 4096^2 67.0 / 53.6; FP16 (bound by instructions)
+// 4096^2 72.8 / 74.8.  Between walls 256 registers would not hold eight.
+inline int stream_levels(unsigned nodes, size_t storage_bytes, bool walls)
+{
+    if (nodes < (walls ? kStreamMinNodesWalls : kStreamMinNodes)) return 0;
+    if (walls || storage_bytes == 2) return 4;
+    return nodes >= (storage_bytes == 8 ? 1u << 22 : 1u << 23) ? 8 : 4;
+}
+
 // Rows per segment for an nx x ny box when the GPU runs `slots` workgroups
 // of the kernel at once.  Every workgroup runs rows + 2 H iterations, so a
 // launch takes about ceil(workgroups / slots) rounds of that many: the rows
 // from 8 to 256 that minimise the product (the fewest among equals).  Long
 // segments re-read fewer rows (8 per segment) but leave part of the last
-// round idle unless the workgroups fill it.  Measured at 4096^2 FP64 (19
+// round idle unless the workgroups fill it.  Measured with four levels at 4096^2 FP64 (19
 // strips, 768 slots): 103 rows (760 workgroups, the rule's choice) 135,500-
 // 136,700 MLUPS; 64 rows (1216) 130,400-132,300; 52 (1501) 131,900; 86
 // (912) 121,400; 120 (665) 128,500.
-inline int stream_rows(int nx, int ny, long long slots)
+inline int stream_rows(int nx, int ny, long long slots, int levels)
 {
     const long long strips = (nx + kStreamStore - 1) / kStreamStore;
     int best = 8;
     long long best_cost = -1;
     for (int rows = 8; rows <= 256; ++rows) {
         const long long wg = strips * ((ny + rows - 1) / rows);
-        const long long cost = (wg + slots - 1) / slots * (rows + 2 * kStreamLevels);
+        const long long cost = (wg + slots - 1) / slots * (rows + 2 * levels);
         if (best_cost < 0 || cost < best_cost) {
             best_cost = cost;
             best = rows;
@@ -76,32 +89,38 @@ inline int stream_rows(int nx, int ny, long long slots)
 }
 
 // Lane i receives v of lane i - 1 (SHIFT = 0x138, wave_shr:1) or of lane
-// i + 1 (SHIFT = 0x130, wave_shl:1); the edge lane keeps its own v.
+// i + 1 (SHIFT = 0x130, wave_shl:1); the edge lane, which is overwritten or
+// not used, receives 0 (keeping its own value would cost a move first).
 template <int SHIFT>
-__device__ __forceinline__ float wave_shift_f(float v)
+__device__ __forceinline__ int lane_shift_bits(int w)
 {
-    int w = __builtin_bit_cast(int, v);
-    w = __builtin_amdgcn_update_dpp(w, w, SHIFT, 0xf, 0xf, false);
-    return __builtin_bit_cast(float, w);
+    return __builtin_amdgcn_update_dpp(0, w, SHIFT, 0xf, 0xf, true);
 }
 
 template <int SHIFT, class C>
 __device__ __forceinline__ C lane_shift(C v)
 {
-    if constexpr (sizeof(C) == 8) return wave_shift<SHIFT>(v);
-    else return wave_shift_f<SHIFT>(v);
+    if constexpr (sizeof(C) == 8) {
+        int2 w = __builtin_bit_cast(int2, v);
+        w.x = lane_shift_bits<SHIFT>(w.x);
+        w.y = lane_shift_bits<SHIFT>(w.y);
+        return __builtin_bit_cast(C, w);
+    } else {
+        return __builtin_bit_cast(C, lane_shift_bits<SHIFT>(__builtin_bit_cast(int, v)));
+    }
 }
 
 // rows: stored rows per workgroup (the last segment may have fewer).  The
 // D2Q9 directions are a = 3 (e_x + 1) + (e_y + 1): a = 0, 1, 2 have
 // e_x = -1, a = 6, 7, 8 e_x = +1; a = 0, 3, 6 have e_y = -1, a = 2, 5, 8
 // e_y = +1.
-template <class S, bool WALLS, bool FORCE, bool COMP, bool NT>
+template <int H, class S, bool WALLS, bool FORCE, bool COMP, bool NT>
 __global__ __launch_bounds__(256) void k_step_ab_stream2d(const S* __restrict__ src, S* __restrict__ dst,
                                                           StepArgs<typename Store<S>::C> p, int rows)
 {
     using C = typename Store<S>::C;
-    constexpr int L = 0, Q = 9, H = kStreamLevels;
+    constexpr int L = 0, Q = 9;
+    static_assert(H <= kStreamHalo, "a level makes one more column on each side invalid");
     const Dims& g = p.g;
     const int t = int(threadIdx.x), lane = t & 63, wave = t >> 6;
     const int x0 = int(blockIdx.x) * kStreamStore;  // first stored column

@@ -74,3 +74,30 @@ def test_graph_replays_between_walls():
         assert graph.wall_force() == eager.wall_force()
     graph.close()
     eager.close()
+
+
+# Periodic boxes of 2^22 nodes (FP64) and 2^23 (FP32): strips of eight steps,
+# ragged columns and rows, a strip wider than the part it stores (nx = 230).
+@pytest.mark.parametrize("dims,storage,comp", [((2100, 2000), "f64", False), ((230, 18300), "f64", True),
+                                               ((2900, 2900), "f32", False)])
+def test_eight_step_strips_equal_one_step_launches(dims, storage, comp):
+    many = _sim(dims, (0, 0, 0), storage, False, comp)[0]
+    one = _sim(dims, (0, 0, 0), storage, False, comp)[0]
+    for n in (8, 13, 23):
+        many.step(n)
+        for _ in range(n):
+            one.step(1)
+        assert torch.equal(many.get_populations(), one.get_populations())
+    many.close()
+    one.close()
+
+
+def test_graph_replays_of_eight_step_strips():
+    graph = _sim((2100, 2000), (0, 0, 0), "f64", False, False, graph=True)[0]
+    eager = _sim((2100, 2000), (0, 0, 0), "f64", False, False)[0]
+    for n in (3, 45, 10, 64):
+        graph.step(n)
+        eager.step(n)
+        assert torch.equal(graph.get_populations(), eager.get_populations())
+    graph.close()
+    eager.close()
