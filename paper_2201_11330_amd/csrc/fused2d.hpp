@@ -1,44 +1,41 @@
 // Several time steps of a D2Q9 box in one launch (two-lattice pattern,
 // temporal blocking in LDS).
 //
-// A 256-item workgroup holds an E x E region of nodes (E = 16: one node per
-// work-item; E = 32: four), loads the stored state of that region once and
-// runs kFuseSteps = 4 steps on it: each step puts the post-collision values
-// into LDS, pulls f_a(x) from x - e_a in LDS (Eq. (propagation)) and
-// collides (Eq. (collision), the collide() of the one-step kernels).  A
-// node's value after 4 steps depends only on nodes within 4 links (Chebyshev
-// distance), so the inner (E - 8) x (E - 8) nodes are exact and are the ones
-// stored; the ring around them is recomputed by the neighbouring workgroups,
-// which replaces a grid-wide barrier by redundant arithmetic.  Region nodes
-// take their coordinates modulo the box, so boxes smaller than a region wrap
-// the same way; across walls nothing pulls from such an image.  Where a pull
-// source is a wall (Eq. (bb)) a node takes its own opposite population, by
-// link bits formed or read once per launch.  With a reduced-precision storage every step rounds its
-// result through the storage type, as a store and reload would, so the state
-// after 4 steps is bit for bit that of 4 one-step launches.
+// A workgroup holds an E x E region of nodes, one per work-item, loads the
+// stored state of that region once and runs up to H steps on it: each step
+// puts the post-collision values into LDS, pulls f_a(x) from x - e_a in LDS
+// (Eq. (propagation)) and collides (Eq. (collision), the collide() of the
+// one-step kernels).  A node's value after H steps depends only on nodes
+// within H links (Chebyshev distance), so the inner (E - 2 H) x (E - 2 H)
+// nodes are exact and are the ones stored; the ring around them is
+// recomputed by the neighbouring workgroups, which replaces a grid-wide
+// barrier by redundant arithmetic.  Region nodes take their coordinates
+// modulo the box, so boxes smaller than a region wrap the same way; across
+// walls nothing pulls from such an image.  Where a pull source is a wall
+// (Eq. (bb)) a node takes its own opposite population, by link bits formed or
+// read once per launch.  With a reduced-precision storage every step rounds
+// its result through the storage type, as a store and reload would, so the
+// state after H steps is bit for bit that of H one-step launches.
 //
 // Why: a small box is latency-bound with one launch per step (128 x 128
 // nodes: 64 workgroups, ~3-4 us per step, most of it one dependent
 // load-collide-store chain), and on large boxes a launch reads and writes
-// the state once per 4 steps (36 B per FP64 update instead of 144) at the
-// price of the ring's arithmetic: 4x the useful collisions with E = 16,
-// 1.78x with E = 32.  Measured on MI355X, FP64: 128^2 12,800-13,300 vs
-// 3,900-5,800 MLUPS (one step per launch); 4096^2 95,000 vs 42,900 MLUPS
-// (E = 32 vs the two-node one-step kernel).  Between walls, us per step
-// against one launch per step: 128^2 4.1 -> 1.8, 512 x 128 with a cylinder
-// 5.2 -> 2.6, 512^2 9.6 -> 5.4, 1000 x 777 22.1 -> 13.6.  4 steps per pass beat 2, 3, 5
-// and 6 on every box from 64^2 to 4096^2.
+// the state once per H steps at the price of the ring's arithmetic, (E / (E -
+// 2 H))^2 of the useful collisions, less what the outer nodes leave out: each
+// step they skip as soon as nothing stored depends on them, whole wavefronts
+// at a time (128^2 FP64 1.38 -> 1.20 us per step, 256^2 1.79 -> 1.53, 512^2
+// around an obstacle 4.43 -> 4.37).  Which E and H: see fuse_regions().
 #pragma once
 
 #include "kernels.hpp"
 
 namespace imexlbm {
 
-constexpr int kFuseSteps = 4;  // steps per launch (halo width)
+constexpr int kFuseSteps = 4;  // steps that every region can take in a launch
 
 // Inner (stored) nodes per region edge.
-template <int E>
-inline constexpr int kFuseInnerOf = E - 2 * kFuseSteps;
+template <int E, int H>
+inline constexpr int kFuseInnerOf = E - 2 * H;
 
 // Placement of the workgroups (one per inner block; gx x gy blocks).  With
 // tw = 0 the launch is a gx x gy grid.  Otherwise it is one-dimensional and
@@ -68,20 +65,46 @@ __device__ __forceinline__ bool fuse_block(const FuseMap& m, int& bx, int& by)
     return bx < m.gx && by < m.gy;
 }
 
-// Choice of region and placement, measured on MI355X (FP64):
-//  * E = 32 (72 KB of LDS per workgroup, 2 waves per SIMD) from
-//    kFuseBigMinBlocks of its 24 x 24 blocks up, on a plain grid: x1.09 at
-//    384^2 (256 blocks), x1.17-1.26 at 512^2, x1.36 at 1000 x 777, x1.38 at
-//    1024^2, x1.47 at 4096^2 over E = 16; with fewer blocks it fills too few
-//    CUs (x0.84 at 320^2, 196 blocks; x0.73 at 256^2).  Its XCD-aware
-//    placement was slower (x0.92-0.99).
-//  * E = 16 otherwise, XCD-aware in tiles of 8 x 8 blocks from
-//    kFuseXcdMinBlocks of its 8 x 8 blocks up: +3 to +21 % from 192^2 to
-//    2048^2, most on ragged boxes; at 256 blocks (128^2) the padding to
-//    whole tiles costs 15 %.  Tiles of 16 x 16 blocks were no better.
-constexpr int kFuseBigMinBlocks = 256;
-constexpr int kFuseXcdMinBlocks = 512;
-constexpr int kFuseXcdTile = 8;
+inline long long fuse_blocks(int nx, int ny, int inner)
+{
+    return (long long)((nx + inner - 1) / inner) * ((ny + inner - 1) / inner);
+}
+
+// Regions of a box, E x E nodes with a ring of H.
+enum FuseRegions { kRegions24x8, kRegions32x8, kRegions32x6, kRegions32x4 };
+
+// Choice of region and placement, measured on MI355X on boxes from 64^2 to
+// 3000 x 2000 (us per step; before: four steps per launch on 16 x 16 regions,
+// from 256 blocks up on 32 x 32 regions of four nodes per work-item):
+//  * 24 x 24 regions with eight steps where their 8 x 8 blocks are at most one
+//    per CU: FP64 128^2 1.47 -> 1.20, FP32 1.33 -> 1.00, FP16 1.27 -> 0.96.
+//  * 32 x 32 regions have 1024 work-items and, in FP64, 72 KB of LDS: two fit a
+//    CU, 32 wavefronts.  With eight steps the launches of boxes of up to 288
+//    blocks pay their latency half as often: FP64 170^2 1.92 -> 1.43, 256^2
+//    2.05 -> 1.52, 512 x 128 around a cylinder 2.37 -> 1.74; FP32 256^2 1.78 ->
+//    1.24.  On larger boxes the ring of eight is too much arithmetic (300^2,
+//    361 blocks, 2.10, 384^2 2.76, between walls 2.63 and 3.56) and six steps
+//    are better: 2.49 -> 1.77, 3.19 -> 2.50, 3.29 -> 2.10, 3.77 -> 3.10; 1000 x
+//    777 10.5 -> 8.3; then four: 1024^2 13.4 -> 11.3 (FP16 10.8 -> 6.8), 900 x
+//    800 between walls 9.6 (six steps: 9.8).
+// XCD-aware tiles of 4 x 4 blocks for rings of eight and six up to 512 blocks:
+// 256^2 2.04 -> 1.78, 300^2 2.43 -> 2.03; but 512^2, 676 blocks, 4.1 -> 4.7: the
+// padding to whole tiles.
+constexpr int kFuseTile = 4;
+constexpr int kFuseXcdMaxBlocks = 512;
+
+inline FuseRegions fuse_regions(int nx, int ny, bool walls)
+{
+    if (fuse_blocks(nx, ny, 8) <= 256) return kRegions24x8;
+    if (fuse_blocks(nx, ny, 16) <= 288) return kRegions32x8;
+    return fuse_blocks(nx, ny, 20) <= (walls ? 1280 : 2000) ? kRegions32x6 : kRegions32x4;
+}
+
+// Steps per launch.
+inline int fuse_levels(FuseRegions r)
+{
+    return r == kRegions24x8 || r == kRegions32x8 ? 8 : r == kRegions32x6 ? 6 : 4;
+}
 
 // The placement of an nx x ny box in blocks of `inner` x `inner` stored
 // nodes: tiles of tile x tile blocks (0: plain grid), and the launch grid
@@ -122,26 +145,29 @@ __device__ __forceinline__ unsigned link_bits_2d(const Dims& g, int x, int y)
     return axis_bits_2d(g, 0, x) | axis_bits_2d(g, 1, y);
 }
 
-// `steps` (1 .. kFuseSteps) is the number of steps of this launch.
-template <int E, class S, bool WALLS, bool FORCE, bool COMP, bool NT>
-__global__ __launch_bounds__(256) void k_step_ab_fused2d(const S* __restrict__ src, S* __restrict__ dst,
-                                                         StepArgs<typename Store<S>::C> p, FuseMap m, int steps)
+// An E x E region with a ring of H nodes, one work-item per node; `steps`
+// (1 .. H) is the number of steps of this launch.  After step s of it only
+// nodes within steps - s links of the stored block are needed, so the others
+// (whole rows, and with them whole wavefronts) skip that step.
+template <int E, int H, class S, bool WALLS, bool FORCE, bool COMP, bool NT>
+__global__ __launch_bounds__((E * E)) void k_step_ab_fused2d(const S* __restrict__ src, S* __restrict__ dst,
+                                                             StepArgs<typename Store<S>::C> p, FuseMap m, int steps)
 {
     using C = typename Store<S>::C;
-    constexpr int L = 0, Q = Lattice<L>::Q, H = kFuseSteps, I = kFuseInnerOf<E>;
-    constexpr int NE = E / 16, NPT = NE * NE;  // nodes per work-item: (tx + 16i, ty + 16j)
-    static_assert(E % 16 == 0 && I >= 1, "region edge must be a multiple of 16 and exceed the ring");
+    constexpr int L = 0, Q = Lattice<L>::Q, I = kFuseInnerOf<E, H>;
+    static_assert(I >= 1, "region edge must exceed the ring");
     int bx, by;
     if (!fuse_block(m, bx, by)) return;  // uniform over the workgroup
     __shared__ C sh[Q][E][E];
     const Dims& g = p.g;
-    const int tx = int(threadIdx.x) & 15, ty = int(threadIdx.x) >> 4;
+    const int lx = int(threadIdx.x) % E, ly = int(threadIdx.x) / E;
     const int TS = g.S;
-    C f[NPT][Q];
-    unsigned bits[NPT];
-#pragma unroll
-    for (int j = 0; j < NPT; ++j) {
-        const int lx = tx + 16 * (j % NE), ly = ty + 16 * (j / NE);
+    // Links to the stored block (none inside it).
+    const int out_x = max(H - lx, lx - (E - 1 - H)), out_y = max(H - ly, ly - (E - 1 - H));
+    const int out = max(out_x, out_y);
+    C f[Q];
+    unsigned bits = 0;
+    if (out <= steps) {
         int gx = (bx * I - H + lx) % g.nx;
         int gy = (by * I - H + ly) % g.ny;
         gx += gx < 0 ? g.nx : 0;
@@ -149,75 +175,58 @@ __global__ __launch_bounds__(256) void k_step_ab_fused2d(const S* __restrict__ s
         const unsigned node = unsigned(gx) + unsigned(g.nx) * unsigned(gy);
         static_for<Q>([&](auto ac) {
             constexpr int a = decltype(ac)::value;
-            f[j][a] = Store<S>::load(src[slot<Q>(a, node, TS)]);
+            f[a] = Store<S>::load(src[slot<Q>(a, node, TS)]);
         });
-        bits[j] = WALLS ? link_bits_2d(g, gx, gy) : 0u;
+        if constexpr (WALLS) bits = link_bits_2d(g, gx, gy);
     }
-    for (int s = 0; s < steps; ++s) {
-#pragma unroll
-        for (int j = 0; j < NPT; ++j) {
-            const int lx = tx + 16 * (j % NE), ly = ty + 16 * (j / NE);
+    for (int left = steps; left > 0; --left) {
+        if (out <= left) {
             static_for<Q>([&](auto ac) {
                 constexpr int a = decltype(ac)::value;
-                sh[a][ly][lx] = f[j][a];
+                sh[a][ly][lx] = f[a];
             });
         }
         __syncthreads();
-        // Pull; a region-edge node reads a clamped (stale) neighbour, which
-        // only reaches nodes outside the stored inner block.
-#pragma unroll
-        for (int j = 0; j < NPT; ++j) {
-            const int lx = tx + 16 * (j % NE), ly = ty + 16 * (j / NE);
+        const bool needed = out < left;  // then out < H: no pull leaves the region
+        if (needed) {
             static_for<Q>([&](auto ac) {
                 constexpr int a = decltype(ac)::value;
                 constexpr int ex = kLattice<L>.e[a][0], ey = kLattice<L>.e[a][1];
-                int sx = lx - ex, sy = ly - ey;
-                if constexpr (ex == 1) sx = sx < 0 ? 0 : sx;
-                if constexpr (ex == -1) sx = sx > E - 1 ? E - 1 : sx;
-                if constexpr (ey == 1) sy = sy < 0 ? 0 : sy;
-                if constexpr (ey == -1) sy = sy > E - 1 ? E - 1 : sy;
-                f[j][a] = sh[a][sy][sx];
+                f[a] = sh[a][ly - ey][lx - ex];
                 if constexpr (WALLS) {  // from a wall: the node's own opposite population
-                    if ((bits[j] >> a) & 1u) f[j][a] = sh[Lattice<L>::opp(a)][ly][lx];
+                    if ((bits >> a) & 1u) f[a] = sh[Lattice<L>::opp(a)][ly][lx];
                 }
             });
         }
         __syncthreads();
-#pragma unroll
-        for (int j = 0; j < NPT; ++j) {
+        if (needed) {
             if constexpr (WALLS) {
-                if (g.nodal >= 0) {
-                    const int lx = tx + 16 * (j % NE), ly = ty + 16 * (j / NE);
-                    nodal_fill<L>(g, wrap_into(bx * I - H + lx, g.nx), wrap_into(by * I - H + ly, g.ny), 0, f[j]);
-                }
+                if (g.nodal >= 0)
+                    nodal_fill<L>(g, wrap_into(bx * I - H + lx, g.nx), wrap_into(by * I - H + ly, g.ny), 0, f);
             }
-            collide<L, C, FORCE, COMP, Store<S>::kDeviation>(f[j], p.c);
+            collide<L, C, FORCE, COMP, Store<S>::kDeviation>(f, p.c);
             if constexpr (!std::is_same_v<S, C>) {
                 static_for<Q>([&](auto ac) {
                     constexpr int a = decltype(ac)::value;
-                    f[j][a] = Store<S>::load(Store<S>::save(f[j][a]));
+                    f[a] = Store<S>::load(Store<S>::save(f[a]));
                 });
             }
         }
     }
-#pragma unroll
-    for (int j = 0; j < NPT; ++j) {
-        const int lx = tx + 16 * (j % NE), ly = ty + 16 * (j / NE);
-        const int ix = lx - H, iy = ly - H;
-        if (ix < 0 || ix >= I || iy < 0 || iy >= I) continue;
-        const int ox = bx * I + ix, oy = by * I + iy;
-        if (ox >= g.nx || oy >= g.ny) continue;
-        if (WALLS && (bits[j] >> 31)) continue;
-        const unsigned own = unsigned(ox) + unsigned(g.nx) * unsigned(oy);
-        // Non-temporal global stores: the nt | sc1 buffer stores of the
-        // one-step kernels measured slower here (128^2: 11,950 vs 12,500-
-        // 13,300 MLUPS; 4096^2: 83,900 vs 89,600-91,000), the written state
-        // being read again, largely from cache, by the next launch.
-        static_for<Q>([&](auto ac) {
-            constexpr int a = decltype(ac)::value;
-            put<NT>(dst + slot<Q>(a, own, TS), Store<S>::save(f[j][a]));
-        });
-    }
+    const int ix = lx - H, iy = ly - H;
+    if (out > 0) return;
+    const int ox = bx * I + ix, oy = by * I + iy;
+    if (ox >= g.nx || oy >= g.ny) return;
+    if (WALLS && (bits >> 31)) return;
+    const unsigned own = unsigned(ox) + unsigned(g.nx) * unsigned(oy);
+    // Non-temporal global stores: the nt | sc1 buffer stores of the
+    // one-step kernels measured slower here (128^2: 11,950 vs 12,500-
+    // 13,300 MLUPS; 4096^2: 83,900 vs 89,600-91,000), the written state
+    // being read again, largely from cache, by the next launch.
+    static_for<Q>([&](auto ac) {
+        constexpr int a = decltype(ac)::value;
+        put<NT>(dst + slot<Q>(a, own, TS), Store<S>::save(f[a]));
+    });
 }
 
 }  // namespace imexlbm

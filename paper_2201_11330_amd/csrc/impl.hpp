@@ -9,8 +9,8 @@
 
 namespace imexlbm {
 
-// A captured run holds whole pairs of fused launches (see eager()).
-static_assert(kGraphSteps % (2 * kFuseSteps) == 0 && kGraphSteps % 16 == 0, "a captured run holds whole pairs of launches");
+// A captured run holds whole pairs of multi-step launches (see eager()).
+static_assert(kGraphSteps % (2 * kFuseSteps) == 0, "graph length must be a multiple of 2 * kFuseSteps");
 
 // Compile-time configuration of the step kernels: walls or masks present,
 // body force, compressible equilibrium (which always takes the force path).
@@ -176,36 +176,45 @@ struct Impl {
         hipLaunchKernelGGL(kernel, grid, c->block, 0, c->stream, src, dst, step_args<typename Store<S>::C>(c), rows);
     }
 
-    // `steps` (2 .. kFuseSteps, or strip_levels) steps of a D2Q9 two-lattice
-    // box in one launch: strips on the largest boxes, else (and for fewer
-    // steps) 32 x 32 regions on large boxes and 16 x 16 regions otherwise
-    // (XCD-aware placement from kFuseXcdMinBlocks blocks up); see
-    // stream2d.hpp and fused2d.hpp.
+    static FuseRegions regions(const lbm_ctx* c)
+    {
+        return fuse_regions(c->nx, c->ny, c->walls);
+    }
+
+    // `steps` (2 .. the steps of the box's regions, or strip_levels) steps of a
+    // D2Q9 two-lattice box in one launch: strips on the largest boxes, else
+    // (and for fewer steps) regions; see stream2d.hpp and fused2d.hpp.
     template <class K>
     static void step_fused2d(lbm_ctx* c, const S* src, S* dst, int steps)
     {
-        constexpr int I32 = kFuseInnerOf<32>, I16 = kFuseInnerOf<16>;
-        const auto blocks = [&](int inner) {
-            return (long long)((c->nx + inner - 1) / inner) * ((c->ny + inner - 1) / inner);
-        };
-        const auto args = step_args<typename Store<S>::C>(c);
-        dim3 grid;
         if (steps == strip_levels(c)) {
             if (steps == 8) {
                 if constexpr (!K::walls && sizeof(S) > 2) step_strips<K, 8>(c, src, dst);
             } else {
                 step_strips<K, 4>(c, src, dst);
             }
-        } else if (blocks(I32) >= kFuseBigMinBlocks) {
-            const FuseMap m = fuse_plan(c->nx, c->ny, I32, 0, &grid);
-            hipLaunchKernelGGL((k_step_ab_fused2d<32, S, K::walls, K::force, K::comp, kNtStores>), grid, c->block, 0,
-                               c->stream, src, dst, args, m, steps);
-        } else {
-            const FuseMap m =
-                fuse_plan(c->nx, c->ny, I16, blocks(I16) >= kFuseXcdMinBlocks ? kFuseXcdTile : 0, &grid);
-            hipLaunchKernelGGL((k_step_ab_fused2d<16, S, K::walls, K::force, K::comp, kNtStores>), grid, c->block, 0,
-                               c->stream, src, dst, args, m, steps);
+            return;
         }
+        switch (regions(c)) {
+        case kRegions24x8: return step_regions<K, 24, 8>(c, src, dst, steps, 0);
+        case kRegions32x8: return step_regions<K, 32, 8>(c, src, dst, steps, kFuseTile);
+        case kRegions32x6: {
+            const bool xcd = fuse_blocks(c->nx, c->ny, 20) <= kFuseXcdMaxBlocks;
+            return step_regions<K, 32, 6>(c, src, dst, steps, xcd ? kFuseTile : 0);
+        }
+        case kRegions32x4: return step_regions<K, 32, 4>(c, src, dst, steps, 0);
+        }
+    }
+
+    // Regions of E x E nodes with a ring of H, placed in tiles of xcd_tile x
+    // xcd_tile blocks per XCD (0: plain grid).
+    template <class K, int E, int H>
+    static void step_regions(lbm_ctx* c, const S* src, S* dst, int steps, int xcd_tile)
+    {
+        dim3 grid;
+        const FuseMap m = fuse_plan(c->nx, c->ny, kFuseInnerOf<E, H>, xcd_tile, &grid);
+        hipLaunchKernelGGL((k_step_ab_fused2d<E, H, S, K::walls, K::force, K::comp, kNtStores>), grid,
+                           dim3(E * E), 0, c->stream, src, dst, step_args<typename Store<S>::C>(c), m, steps);
     }
 
     // Two steps per launch through the planes of a 3D box (march3d.hpp): FP64
@@ -288,14 +297,14 @@ struct Impl {
             }
         }
         if constexpr (L == 0) {
-            // D2Q9, two lattices: launches of up to kFuseSteps steps.  Where
-            // graphs are captured, in pairs of kFuseSteps steps, so that the
-            // current buffer keeps following the parity of the step count,
-            // and the remainder one step per launch; a last single step is
-            // always a one-step launch.  Large boxes in 16-bit storage between
-            // walls on the axes are left to the one-step kernel (2048^2 FP16:
-            // 32.8 us per step, strips 34.8 with halfway and 38.6 with nodal
-            // walls; with a mask 40.3 and 33.8).
+            // D2Q9, two lattices: launches of up to eight steps.  Where graphs
+            // are captured, in pairs of equal launches, so that the current
+            // buffer keeps following the parity of the step count, and the
+            // remainder one step per launch; a last single step is always a
+            // one-step launch.  Boxes in 16-bit storage between walls
+            // on the axes that would take strips are left to the one-step
+            // kernel (2048^2 FP16: 32.8 us per step, strips 34.8 with halfway
+            // and 38.6 with nodal walls; with a mask 40.3 and 33.8).
             if (!c->aa && !(sizeof(S) == 2 && c->walls && !c->links && c->N >= kStreamMinNodesWalls)) {
                 const auto fuse = [&](int steps) {
                     const S* src = static_cast<const S*>(c->buf[c->cur]);
@@ -305,7 +314,8 @@ struct Impl {
                     c->steps += steps;
                     i += steps;
                 };
-                const int most = strip_levels(c) ? strip_levels(c) : kFuseSteps;
+                const int strips = strip_levels(c);
+                const int most = strips ? strips : fuse_levels(regions(c));
                 for (int k = most;; k = kFuseSteps) {
                     while (n - i >= 2 * k) {
                         fuse(k);
@@ -315,7 +325,8 @@ struct Impl {
                 }
                 if (!c->use_graph) {
                     if (n - i >= most) fuse(most);
-                    while (n - i >= 2) fuse(n - i < kFuseSteps ? n - i : kFuseSteps);
+                    const int rest = strips ? kFuseSteps : most;
+                    while (n - i >= 2) fuse(n - i < rest ? n - i : rest);
                 }
             }
         }

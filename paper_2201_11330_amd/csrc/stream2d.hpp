@@ -41,13 +41,15 @@ namespace imexlbm {
 constexpr int kStreamCols = 256;  // columns per workgroup, one per work-item
 constexpr int kStreamHalo = 16;   // loaded columns on each side of the stored ones
 constexpr int kStreamStore = kStreamCols - 2 * kStreamHalo;  // 224 stored columns
-// Boxes of at least kStreamMinNodes nodes take these launches (smaller ones
-// the regions of fused2d.hpp).
-constexpr unsigned kStreamMinNodes = 1u << 20;
-// Between walls (FP64: 196 registers instead of 138, two wavefronts per SIMD
-// instead of three) from twice as many: 1024^2 17.3 us per step, regions
-// 16.8; 2048^2 47.0, regions 56.7, the one-step kernel 95.4.
-constexpr unsigned kStreamMinNodesWalls = 1u << 21;
+// Smaller boxes take the regions of fused2d.hpp.  us per step, strips against
+// regions: FP64 1024^2 14.7 / 11.4, 1500 x 1100 17.4 / 17.3, 2048 x 1024 20.5 /
+// 21.7, 2048^2 32.8 / 42.7; FP32 1024^2 8.4 / 7.6, 2048 x 1024 12.6 / 13.3;
+// FP16 1500^2 16.0 / 12.8, 2048^2 23.5 / 23.8.  Between walls (FP64: 218
+// registers instead of 138, two wavefronts per SIMD instead of three) FP64
+// 1500^2 26.3 / 25.5, 2048^2 45.0 / 46.2, FP32 2048^2 27.5 / 31.3.
+constexpr unsigned kStreamMinNodes = 1u << 21;
+constexpr unsigned kStreamMinNodes16 = 1u << 22;     // 16-bit storage
+constexpr unsigned kStreamMinNodesWalls = 3u << 20;  // between walls
 
 // Steps per launch of a box (0: it does not take strips).  Eight steps read
 // and write the state half as often as four, but hold twice the registers
@@ -58,7 +60,7 @@ constexpr unsigned kStreamMinNodesWalls = 1u << 21;
 // 4096^2 72.8 / 74.8.  Between walls 256 registers would not hold eight.
 inline int stream_levels(unsigned nodes, size_t storage_bytes, bool walls)
 {
-    if (nodes < (walls ? kStreamMinNodesWalls : kStreamMinNodes)) return 0;
+    if (nodes < (walls ? kStreamMinNodesWalls : storage_bytes == 2 ? kStreamMinNodes16 : kStreamMinNodes)) return 0;
     if (walls || storage_bytes == 2) return 4;
     return nodes >= (storage_bytes == 8 ? 1u << 22 : 1u << 23) ? 8 : 4;
 }

@@ -12,10 +12,10 @@ from parity_utils import inputs, rel_err, run_oracle
 
 pytestmark = pytest.mark.gpu
 
-# 16 x 16 regions on a plain grid and in XCD-aware tiles, 32 x 32 regions,
-# boxes smaller than a region, strips (2^21 nodes and more) with ragged
-# columns and rows.
-DIMS = [(7, 5), (40, 30), (130, 97), (200, 170), (600, 500), (1500, 1400), (230, 9200)]
+# Every region: 24 x 24 (boxes smaller than it among them), 32 x 32 with
+# eight, six (in XCD-aware tiles and on a plain grid) and four steps; strips
+# (periodic 2^21 nodes and more) with ragged columns and rows.
+DIMS = [(7, 5), (40, 30), (130, 97), (200, 170), (260, 250), (300, 270), (600, 500), (1500, 1400), (230, 9200)]
 BCS = [(0, 0, 0), (0, 1, 0), (2, 1, 0), (1, 2, 0), (0, 3, 0), (3, 1, 0)]
 
 
@@ -72,6 +72,27 @@ def test_graph_replays_between_walls():
         eager.step(n)
         assert torch.equal(graph.get_populations(), eager.get_populations())
         assert graph.wall_force() == eager.wall_force()
+    graph.close()
+    eager.close()
+
+
+# Between walls strips are taken from 3 * 2^20 nodes up.
+@pytest.mark.parametrize("bc,mask", [((0, 1, 0), False), ((2, 1, 0), True), ((0, 3, 0), False)])
+@pytest.mark.parametrize("storage", ["f64", "f32", "f16"])
+@pytest.mark.parametrize("dims", [(230, 13700), (2000, 1600)], ids=lambda d: f"{d[0]}x{d[1]}")
+def test_strips_between_walls_equal_one_step_launches(dims, bc, mask, storage):
+    test_multi_step_launches_equal_one_step_launches(dims, bc, mask, storage, False)
+
+
+# Graphs of pairs of eight- and of six-step launches.
+@pytest.mark.parametrize("dims", [(97, 120), (260, 250), (300, 270)], ids=lambda d: f"{d[0]}x{d[1]}")
+def test_graph_replays_of_regions(dims):
+    graph = _sim(dims, (0, 1, 0), "f64", True, False, graph=True)[0]
+    eager = _sim(dims, (0, 1, 0), "f64", True, False)[0]
+    for n in (3, 45, 10, 64):
+        graph.step(n)
+        eager.step(n)
+        assert torch.equal(graph.get_populations(), eager.get_populations())
     graph.close()
     eager.close()
 
