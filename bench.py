@@ -161,7 +161,7 @@ def run_channel(steps=200, warmup=10, nx=512, ny=128, nz=128, tau=0.9, g=1e-6, n
     return {"workload": f"D3Q19 {nx}x{ny}x{nz} channel, {walls} y=0,{ny - 1}, g_x={g}, tau={tau}, "
                         f"FP64 AB, {steps} steps",
             "mlups": round(mlups, 1), "mlups_fluid_nodes": round(mlups * fluid / ny, 1),
-            "achieved_gbs": round(304 * nodes * steps / (ms * 1e-3) / 1e9, 1)}
+            "achieved_gbs": round(152 * nodes * steps / (ms * 1e-3) / 1e9, 1)}  # two steps per launch
 
 
 def run_channel_sustained(steps=20000, chunk=1000, warmup=10, nx=512, ny=128, nz=128, tau=0.9,
@@ -200,8 +200,8 @@ def run_channel_sustained(steps=20000, chunk=1000, warmup=10, nx=512, ny=128, nz
     return {"workload": f"D3Q19 {nx}x{ny}x{nz} channel, solid planes y=0,{ny - 1}, g_x={g}, "
                         f"tau={tau}, FP64 AB, {chunk * nchunks} steps ({nchunks} x lbm_step({chunk}))",
             "mlups": round(mlups, 1),
-            "achieved_gbs": round(304 * nodes * chunk * nchunks / (total * 1e-3) / 1e9, 1),
-            "frac": round(304 * nodes * chunk * nchunks / (total * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
+            "achieved_gbs": round(152 * nodes * chunk * nchunks / (total * 1e-3) / 1e9, 1),
+            "frac": round(152 * nodes * chunk * nchunks / (total * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
             "us_per_step": round(total * 1e3 / (chunk * nchunks), 2),
             "chunk_mlups_first_last": [round(per[0], 1), round(per[-1], 1)],
             "chunk_mlups_min_max": [round(min(per), 1), round(max(per), 1)],
@@ -212,7 +212,7 @@ def run_taylor_green_sustained(n=256, steps=2000, chunk=250, warmup=100, tau=0.6
     """The headline workload (D3Q19 n^3 periodic FP64 Taylor-Green with
     1e-6 noise, seed 2) for `steps` steps issued as lbm_step(chunk) calls,
     an event on the launch stream after each: the sustained rate of the
-    benchmark's step kernel and how it changes over the run."""
+    two-step launches and how it changes over the run."""
     import torch
 
     from paper_2201_11330_amd import lbm
@@ -239,10 +239,10 @@ def run_taylor_green_sustained(n=256, steps=2000, chunk=250, warmup=100, tau=0.6
     ms = [ev[i].elapsed_time(ev[i + 1]) for i in range(nchunks)]
     per = [nodes * chunk / (m * 1e-3) / 1e6 for m in ms]
     total = sum(ms)
-    gbs = 304 * nodes * chunk * nchunks / (total * 1e-3) / 1e9
+    gbs = 152 * nodes * chunk * nchunks / (total * 1e-3) / 1e9  # two steps per launch
     return {"workload": f"D3Q19 {n}^3 periodic FP64 Taylor-Green, tau={tau}, {chunk * nchunks} steps "
                         f"({nchunks} x lbm_step({chunk})) after {warmup} untimed",
-            "kernel": step_kernel_name(n, "f64", "ab"),
+            "kernel": "k_step_ab_march (2 steps per launch)",
             "mlups": round(nodes * chunk * nchunks / (total * 1e-3) / 1e6, 1),
             "achieved_gbs": round(gbs, 1), "frac": round(gbs / HBM_PEAK_GBS, 4),
             "us_per_step": round(total * 1e3 / (chunk * nchunks), 2),
@@ -354,6 +354,8 @@ def run_paper_sphere(steps=100, warmup=5, storage="f64"):
     sim.close()
     nodes = nx * ny * nz
     blu = 2 * 27 * STORAGE_BYTES[storage] + 4  # + the 4-byte link bits of the mask
+    if storage == "f64":
+        blu /= 2  # two steps per launch
     return {"workload": "D3Q27 512x128x128, sphere r=8 at (64,64,64), periodic, g_x=1e-6, "
                         f"tau=0.6, {storage} AB, {steps} steps",
             "mlups": round(nodes * steps / (ms * 1e-3) / 1e6, 1),
@@ -379,7 +381,7 @@ PAPER_CONTEXT = {
 
 def run_small_2d(n=128, steps=1000, tau=0.8):
     """D2Q9 n^2 periodic Taylor-Green (U0 = 0.01), the launch-bound small
-    workload: MLUPS of lbm_step(steps) (launches of four steps each, LDS
+    workload: MLUPS of lbm_step(steps) (launches of eight steps each, LDS
     temporal blocking) issued eagerly and as captured-graph replays."""
     import torch
 
@@ -388,7 +390,7 @@ def run_small_2d(n=128, steps=1000, tau=0.8):
 
     rho, u = W.taylor_green_2d(n, U0=0.01)
     out = {"workload": f"D2Q9 {n}^2 periodic Taylor-Green, tau={tau}, {steps} steps, FP64 AB",
-           "kernel": "k_step_ab_fused2d<16> (4 steps per launch, 16x16-node regions)"}
+           "kernel": "k_step_ab_fused2d<24, 8> (8 steps per launch, 24x24-node regions)"}
     for graph in (False, True):
         sim = lbm.LBM(lbm.D2Q9, n, n, 1, tau, graph=graph)
         best = None
@@ -410,11 +412,11 @@ def run_small_2d(n=128, steps=1000, tau=0.8):
 
 def run_large_2d(n=4096, steps=200, warmup=400, tau=0.8):
     """D2Q9 n^2 periodic Taylor-Green (U0 = 0.01), FP64 AB: a box far larger
-    than the caches, where the four-step launches (strips streamed up the
-    rows) read and write the state once per four steps (36 B per update)
+    than the caches, where the eight-step launches (strips streamed up the
+    rows) read and write the state once per eight steps (18 B per update)
     against the 144 B a one-step pass moves.  400 untimed steps: after the
-    host-side set-up leaves the GPU idle, these launches take ~50 of them
-    (~30 ms) to reach their steady duration (670 -> 487 us)."""
+    host-side set-up leaves the GPU idle, these launches take
+    ~30 ms to reach their steady duration."""
     import torch
 
     from paper_2201_11330_amd import lbm
@@ -436,9 +438,9 @@ def run_large_2d(n=4096, steps=200, warmup=400, tau=0.8):
     mlups = n * n * steps / (ms * 1e-3) / 1e6
     one_step_bound = HBM_PEAK_GBS * 1e3 / 144.0
     return {"workload": f"D2Q9 {n}^2 periodic Taylor-Green, tau={tau}, {steps} steps, FP64 AB",
-            "kernel": "k_step_ab_stream2d (4 steps per launch, strips of 224 columns streamed "
+            "kernel": "k_step_ab_stream2d (8 steps per launch, strips of 224 columns streamed "
                       "up row segments)",
-            "mlups": round(mlups, 1), "bytes_per_update_moved": 36,
+            "mlups": round(mlups, 1), "bytes_per_update_moved": 18,
             "one_step_hbm_bound_mlups": round(one_step_bound, 1),
             "vs_one_step_hbm_bound": round(mlups / one_step_bound, 3)}
 

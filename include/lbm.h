@@ -180,8 +180,9 @@ lbm_status lbm_get_populations(lbm_ctx* ctx, double* f);
 
 /*
  * Advances n >= 0 time steps.  Asynchronous on the bound stream.  A D2Q9
- * two-lattice box runs up to four steps per launch; a large 3D two-lattice box in FP64 or
- * FP32 storage runs two steps per launch; the rest run one step per launch.
+ * two-lattice box runs up to eight steps per launch; a large 3D two-lattice
+ * box in FP64 or FP32 storage runs two steps per launch; the rest run one step
+ * per launch.
  * The state after any n is bit for bit that of n one-step launches.
  */
 lbm_status lbm_step(lbm_ctx* ctx, int n);
