@@ -184,6 +184,10 @@ lbm_status lbm_get_populations(lbm_ctx* ctx, double* f);
  * box in FP64 or FP32 storage runs two steps per launch; the rest run one step
  * per launch.
  * The state after any n is bit for bit that of n one-step launches.
+ * Calls on a stream that the caller is capturing are recorded into the
+ * caller's graph.  Replays continue from the state they find, also with other
+ * calls between them, when n is even and the number of steps taken has the
+ * parity it had at the capture.
  */
 lbm_status lbm_step(lbm_ctx* ctx, int n);
 

@@ -68,6 +68,15 @@ struct lbm_ctx {
     int device = -1;  // current device at lbm_bind
     void* buf[2] = {nullptr, nullptr};
     int cur = 0;  // AB: buffer holding the current state
+    // The current buffer follows the parity of the step count: it is
+    // even_buf after an even number of steps and the other one after an odd
+    // number.  Needed where launches are recorded to be replayed, which read
+    // and write the buffers they were recorded with: with LBM_FLAG_GRAPH, and
+    // from the first call on that a caller captures into a graph of its own
+    // (note_capture).  Elsewhere a launch of several steps may leave the
+    // state in either buffer.
+    bool by_parity = false;
+    int even_buf = 0;
     hipStream_t stream = nullptr;
     bool state_valid = false;
     long long steps = 0;

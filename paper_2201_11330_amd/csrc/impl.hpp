@@ -282,9 +282,9 @@ struct Impl {
         int i = 0;
         if constexpr (kMarch) {
             if (takes_march(c)) {
-                // In pairs of launches where graphs are captured, so that the
-                // current buffer keeps following the parity of the steps.
-                const int launches = c->use_graph ? 2 : 1;
+                // In pairs of launches where the current buffer has to
+                // follow the parity of the steps.
+                const int launches = c->by_parity ? 2 : 1;
                 for (; n - i >= 2 * launches; i += 2 * launches) {
                     for (int h = 0; h < launches; ++h) {
                         const S* src = static_cast<const S*>(c->buf[c->cur]);
@@ -297,11 +297,10 @@ struct Impl {
             }
         }
         if constexpr (L == 0) {
-            // D2Q9, two lattices: launches of up to eight steps.  Where graphs
-            // are captured, in pairs of equal launches, so that the current
-            // buffer keeps following the parity of the step count, and the
-            // remainder one step per launch; a last single step is always a
-            // one-step launch.  Boxes in 16-bit storage between walls
+            // D2Q9, two lattices: launches of up to eight steps.  Where the
+            // current buffer has to follow the parity of the step count, in
+            // pairs of equal launches, and the remainder one step per launch;
+            // a last single step is always a one-step launch.  Boxes in 16-bit storage between walls
             // on the axes that would take strips are left to the one-step
             // kernel (2048^2 FP16: 32.8 us per step, strips 34.8 with halfway
             // and 38.6 with nodal walls; with a mask 40.3 and 33.8).
@@ -321,9 +320,9 @@ struct Impl {
                         fuse(k);
                         fuse(k);
                     }
-                    if (k == kFuseSteps || !c->use_graph) break;
+                    if (k == kFuseSteps || !c->by_parity) break;
                 }
-                if (!c->use_graph) {
+                if (!c->by_parity) {
                     if (n - i >= most) fuse(most);
                     const int rest = strips ? kFuseSteps : most;
                     while (n - i >= 2) fuse(n - i < rest ? n - i : rest);

@@ -101,6 +101,26 @@ lbm_status need_state(const lbm_ctx* c)
     return LBM_OK;
 }
 
+// Called by every operation that a caller can capture into a graph of its
+// own, before it reads or writes the current buffer.  The graph replays with
+// the buffers of the capture, and between replays the caller may take other
+// steps, import a new state or replay other graphs of the context: that works
+// as long as the same step counts, even or odd, always have the same buffer.
+// So from the first captured call on they do.  (The null stream cannot be
+// captured.)
+void note_capture(lbm_ctx* c)
+{
+    if (c->aa || c->by_parity || !c->stream) return;
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &status) != hipSuccess) {
+        (void)hipGetLastError();
+        return;
+    }
+    if (status == hipStreamCaptureStatusNone) return;
+    c->by_parity = true;
+    c->even_buf = c->steps & 1 ? 1 - c->cur : c->cur;
+}
+
 // Checks that p is device (or managed) memory on the current device and,
 // when bytes > 0, that the allocation holding p extends at least bytes past
 // it, so that no kernel of the call can touch memory outside it.
@@ -232,6 +252,7 @@ lbm_status lbm_create(lbm_ctx** out, lbm_lattice lattice, int nx, int ny, int nz
     c->flags = flags;
     c->aa = flags & LBM_FLAG_AA;
     c->use_graph = flags & LBM_FLAG_GRAPH;
+    c->by_parity = c->use_graph;
     c->walls = b[0] != LBM_PERIODIC || b[1] != LBM_PERIODIC || b[2] != LBM_PERIODIC;
     c->force = has_force;
     c->comp = flags & LBM_FLAG_COMPRESSIBLE;
@@ -290,8 +311,9 @@ lbm_status lbm_init_equilibrium(lbm_ctx* c, const double* rho, const double* u, 
     if ((st = check_device_ptr(rho, "rho", false, field))) return st;
     if ((st = check_device_ptr(u, "u", false, 3 * field))) return st;
     if ((st = check_device_ptr(noise, "noise", true, size_t(c->Q) * field))) return st;
+    note_capture(c);
     c->steps = 0;
-    c->cur = 0;
+    c->cur = c->even_buf;
     c->state_valid = false;
     if ((st = c->ops->import(c, nullptr, rho, u, noise))) return st;
     c->state_valid = true;
@@ -303,8 +325,9 @@ lbm_status lbm_set_populations(lbm_ctx* c, const double* f)
     lbm_status st = need_bound(c);
     if (st) return st;
     if ((st = check_device_ptr(f, "f", false, sizeof(double) * size_t(c->Q) * c->N))) return st;
+    note_capture(c);
     c->steps = 0;
-    c->cur = 0;
+    c->cur = c->even_buf;
     c->state_valid = false;
     if ((st = c->ops->import(c, f, nullptr, nullptr, nullptr))) return st;
     c->state_valid = true;
@@ -316,6 +339,7 @@ lbm_status lbm_get_populations(lbm_ctx* c, double* f)
     lbm_status st = need_state(c);
     if (st) return st;
     if ((st = check_device_ptr(f, "f", false, sizeof(double) * size_t(c->Q) * c->N))) return st;
+    note_capture(c);
     return c->ops->export_f(c, f);
 }
 
@@ -324,6 +348,7 @@ lbm_status lbm_step(lbm_ctx* c, int n)
     lbm_status st = need_state(c);
     if (st) return st;
     if (n < 0) return fail(LBM_EINVAL, "n = %d < 0", n);
+    note_capture(c);
     return c->ops->step(c, n);
 }
 
@@ -335,6 +360,7 @@ lbm_status lbm_moments(lbm_ctx* c, void* rho, void* u, int out_is_f32)
     if ((st = check_device_ptr(rho, "rho", true, field))) return st;
     if ((st = check_device_ptr(u, "u", true, 3 * field))) return st;
     if (!rho && !u) return LBM_OK;
+    note_capture(c);
     return c->ops->moments(c, rho, u, out_is_f32);
 }
 
@@ -371,6 +397,7 @@ lbm_status lbm_reduce_noalloc(lbm_ctx* c, double* result)
                     c->device);
     double* ptr = nullptr;
     if ((st = scratch_address(dev, &ptr))) return st;
+    note_capture(c);
     return c->ops->reduce(c, ptr, result);
 }
 
@@ -409,6 +436,7 @@ lbm_status lbm_forward_record(lbm_ctx* c, int n, int k, void* ckpt)
     if (n == 0) return LBM_OK;
     const size_t bytes = lbm_buffer_bytes(c);
     if ((st = check_device_ptr(ckpt, "ckpt", false, size_t(n / k) * bytes))) return st;
+    note_capture(c);
     char* ck = static_cast<char*>(ckpt);
     for (int s = 0; s < n / k; ++s) {
         LBM_HIP(hipMemcpyAsync(ck + size_t(s) * bytes, c->buf[c->cur], bytes, hipMemcpyDeviceToDevice,
