@@ -103,7 +103,8 @@ struct lbm_ctx {
     // Rows per segment of the streamed D2Q9 launches (0: not planned yet).
     int stream_rows = 0;
 
-    // Planes per segment of the two-step 3D launches (0: not planned yet).
+    // Planes per segment of the two-step 3D launches (0: not decided yet, -1:
+    // the box takes one-step launches).
     int march_planes = 0;
 
     // LBM_FLAG_GRAPH: kGraphSteps steps captured once, replayed by lbm_step.

@@ -221,13 +221,13 @@ struct Impl {
     // and FP32 storage.
     static constexpr bool kMarch = L != 0 && (std::is_same_v<S, double> || std::is_same_v<S, float>);
 
-    static constexpr bool kMarchWallsToo = L == 1 || sizeof(S) == 8;
+    static constexpr bool kMarchWallsToo = L == 1 || sizeof(S) == 8;  // else march_route refuses them
 
     template <class K>
     static void step_march(lbm_ctx* c, const S* src, S* dst)
     {
         if constexpr (!K::walls) step_march_of<K, kMarchOpen>(c, src, dst);
-        else if constexpr (!kMarchWallsToo) return;  // takes_march excludes it
+        else if constexpr (!kMarchWallsToo) return;
         else if (c->nodal >= 0) step_march_of<K, kMarchNodal>(c, src, dst);
         else if (c->links) step_march_of<K, kMarchMask>(c, src, dst);
         else step_march_of<K, kMarchAxes>(c, src, dst);
@@ -235,46 +235,34 @@ struct Impl {
     template <class K, int WK>
     static void step_march_of(lbm_ctx* c, const S* src, S* dst)
     {
-        constexpr int threads = kMarchThreads<L>, most_rows = kMarchRows<L>;
         const auto kernel = k_step_ab_march<L, S, WK, K::force, K::comp>;
         MarchMap m;
-        m.tiles_x = (c->nx + kMarchCols - 1) / kMarchCols;
-        m.tiles_y = (c->ny + most_rows - 1) / most_rows;
-        m.rows = (c->ny + m.tiles_y - 1) / m.tiles_y;
-        const long long cols = (long long)m.tiles_x * m.tiles_y;
+        m.p = march_plan(march_box(c), c->march_planes);
+        m.total = m.p.tiles_x * m.p.tiles_y * ((c->nz + m.p.planes - 1) / m.p.planes);
+        m.chunk = (m.total + 7) / 8;
+        hipLaunchKernelGGL(kernel, dim3(unsigned(m.chunk) * 8), dim3(kMarchThreads<L>), 0, c->stream, src, dst,
+                           step_args<S>(c), m);
+    }
+
+    static MarchBox march_box(const lbm_ctx* c)
+    {
+        return {L, sizeof(S), {c->nx, c->ny, c->nz}, {c->bc[0], c->bc[1], c->bc[2]}, c->links != nullptr, c->comp};
+    }
+
+    // Whether the box takes the two-step launches (march_route); decided at
+    // the first step.
+    static bool takes_march(lbm_ctx* c)
+    {
+        if (c->aa) return false;
         if (c->march_planes == 0) {
             int cus = 0;
             if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess || cus < 1) {
                 (void)hipGetLastError();
                 cus = 256;
             }
-            c->march_planes = march_planes(c->nz, cols, (long long)kMarchPerCu<S> * cus);
+            c->march_planes = march_route(march_box(c), cus);
         }
-        m.planes = c->march_planes;
-        m.total = int(cols * ((c->nz + m.planes - 1) / m.planes));
-        m.chunk = (m.total + 7) / 8;
-        hipLaunchKernelGGL(kernel, dim3(unsigned(m.chunk) * 8), dim3(threads), 0, c->stream, src, dst,
-                           step_args<S>(c), m);
-    }
-
-    // Whether the box takes the two-step launches: decided by measurement,
-    // one-step against two-step launches on boxes from 40^3 to 512^2 x 40.
-    //   * The lanes of a row are padded to 64 there and to a power of two or
-    //     a multiple of 256 in the one-step kernels; where the two-step
-    //     padding is larger (nx <= 32) it lost (x0.5-0.9).
-    //   * Small boxes leave CUs idle or make segments of a few planes, which
-    //     repeat level 1 of two more each.  FP64: x0.8-1.0 up to 56^3,
-    //     x1.02-1.17 from 64^3, x1.3 and more from 90^3; between walls
-    //     x0.8-1.0 below 2^19 nodes (D3Q27: 2^20) and x1.05-1.3 above.
-    //     FP32: x0.8-1.08 up to 128 x 64 x 64, x1.1-1.8 from 5 * 2^17 nodes;
-    //     between walls from 2^21 (x1.03-1.46), D3Q27 not at all.
-    //   * Boxes of fewer than 4 planes: 512 x 512 x 2 x0.89.
-    static bool takes_march(const lbm_ctx* c)
-    {
-        const unsigned lanes = unsigned((c->nx + 63) / 64) * 64, one_step = c->grid.x << c->bx_shift;
-        if (c->aa || lanes > one_step || c->nz < 4 || (unsigned long long)c->nx * c->ny > kMarchMaxPlane) return false;
-        if (sizeof(S) == 8) return c->N >= (!c->walls ? 1u << 18 : L == 1 ? 1u << 19 : 1u << 20);
-        return c->walls ? kMarchWallsToo && c->N >= 1u << 21 : c->N >= 5u << 17;
+        return c->march_planes > 0;
     }
 
     static lbm_status eager(lbm_ctx* c, int n)

@@ -411,7 +411,7 @@ lbm_status lbm_set_solid(lbm_ctx* c, const unsigned char* solid)
     if (c->graph_exec) return fail(LBM_ESTATE, "lbm_set_solid after a graph was captured");
     if (!c->links) LBM_HIP(hipMalloc(&c->links, sizeof(unsigned) * size_t(c->N)));
     c->walls = true;
-    c->stream_rows = 0;  // another kernel, another plan
+    c->stream_rows = c->march_planes = 0;  // another kernel, another plan
     c->state_valid = false;
     return c->ops->build_links(c, solid);
 }

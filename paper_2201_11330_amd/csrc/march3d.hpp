@@ -49,62 +49,26 @@
 #pragma once
 
 #include "kernels.hpp"
+#include "routes.hpp"
 
 namespace imexlbm {
-
-constexpr int kMarchCols = 64;  // stored columns per workgroup, one per lane
 
 // What stops a population on its way: nothing (periodic box), walls on the
 // axes, walls of a solid mask (link bits), or walls on the axes or of a mask
 // with a nodal-wall axis among them.
 enum MarchWalls : int { kMarchOpen = 0, kMarchAxes = 1, kMarchMask = 2, kMarchNodal = 3 };
 
-// Wavefronts per workgroup: one per row of level 1 and one for the two edge
-// columns; 16, or as many as LDS holds rows for.
 template <int L>
-inline constexpr int kMarchWaves = L == 2 ? 12 : 16;
+inline constexpr int kMarchWaves = march_waves(L);
 template <int L>
 inline constexpr int kMarchThreads = kMarchWaves<L> * 64;
-template <int L>
-inline constexpr int kMarchRows = kMarchWaves<L> - 3;  // stored rows of a tile at most
-
-// Workgroups per CU that the registers are shared out for: LDS holds one
-// with FP64 and two with FP32.
-template <class S>
-inline constexpr int kMarchPerCu = sizeof(S) == 8 ? 1 : 2;
 template <int L, class S>
-inline constexpr int kMarchWavesPerSimd = kMarchWaves<L> * kMarchPerCu<S> / 4;
-
-// Largest plane: the byte offset of a population in a plane fits 32 bits and
-// the tile number in a plane 24.
-constexpr unsigned kMarchMaxPlane = 1u << 24;
+inline constexpr int kMarchWavesPerSimd = kMarchWaves<L> * march_per_cu(sizeof(S)) / 4;
 
 struct MarchMap {
-    int tiles_x, tiles_y;  // tiles of kMarchCols columns and `rows` rows
-    int rows;              // stored rows per tile
-    int planes;            // stored planes per segment
+    MarchPlan p;
     int total, chunk;      // workgroups, and how many of them each XCD gets
 };
-
-// Planes per segment when `cols` columns of tiles cover a plane and the GPU
-// runs `slots` workgroups at once: a launch takes about ceil(workgroups /
-// slots) rounds of planes + 2 iterations and the start of the pipeline, so
-// the planes that minimise the product (the fewest among equals).
-// 256^3 FP64 (80 columns, 256 slots): 86 planes, 240 workgroups, 467 us.
-inline int march_planes(int nz, long long cols, long long slots)
-{
-    int best = 1;
-    long long best_cost = -1;
-    for (int planes = 1; planes <= nz; ++planes) {
-        const long long wg = cols * ((nz + planes - 1) / planes);
-        const long long cost = (wg + slots - 1) / slots * (planes + 3);
-        if (best_cost < 0 || cost < best_cost) {
-            best_cost = cost;
-            best = planes;
-        }
-    }
-    return best;
-}
 
 template <int L>
 struct MarchDirs {
@@ -182,11 +146,11 @@ k_step_ab_march(const S* __restrict__ src, S* __restrict__ dst, StepArgs<S> p, M
     // tiles, whose rings overlap.
     const int k = int(blockIdx.x & 7) * m.chunk + int(blockIdx.x >> 3);
     if (k >= m.total) return;
-    const int x0 = (k % m.tiles_x) * kMarchCols;
-    const int y0 = (k / m.tiles_x % m.tiles_y) * m.rows;
-    const int z0 = (k / (m.tiles_x * m.tiles_y)) * m.planes;
-    const int z1 = min(z0 + m.planes, g.nz);
-    const int rows = min(m.rows, g.ny - y0);
+    const int x0 = (k % m.p.tiles_x) * kMarchCols;
+    const int y0 = (k / m.p.tiles_x % m.p.tiles_y) * m.p.rows;
+    const int z0 = (k / (m.p.tiles_x * m.p.tiles_y)) * m.p.planes;
+    const int z1 = min(z0 + m.p.planes, g.nz);
+    const int rows = min(m.p.rows, g.ny - y0);
     const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6), lane = int(threadIdx.x) & 63;
     const bool edge = wave == R;  // lanes 0-31: rows of the column on the left, 32-63: on the right
     const int row = edge ? min(lane & 31, R - 1) : wave;

@@ -18,8 +18,8 @@ pytestmark = pytest.mark.gpu
 CASES = [
     # lattice, dims, storage, bc, solid, aa, steps per replay
     (W.D3Q19, (64, 64, 64), "f64", (0, 0, 0), False, False, 2),
-    (W.D3Q19, (100, 90, 80), "f32", (0, 0, 0), False, False, 6),
-    (W.D3Q27, (130, 91, 90), "f64", (0, 1, 0), True, False, 4),
+    (W.D3Q19, (129, 118, 97), "f32", (0, 0, 0), False, False, 6),
+    (W.D3Q27, (257, 90, 210), "f64", (0, 1, 0), True, False, 4),
     (W.D2Q9, (128, 128, 1), "f64", (0, 0, 0), False, False, 8),
     (W.D2Q9, (260, 250, 1), "f16", (0, 1, 0), True, False, 2),
     (W.D2Q9, (300, 270, 1), "f64", (0, 0, 0), False, False, 14),
