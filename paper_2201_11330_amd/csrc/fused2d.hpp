@@ -28,10 +28,9 @@
 #pragma once
 
 #include "kernels.hpp"
+#include "routes.hpp"
 
 namespace imexlbm {
-
-constexpr int kFuseSteps = 4;  // steps that every region can take in a launch
 
 // Inner (stored) nodes per region edge.
 template <int E, int H>
@@ -65,47 +64,6 @@ __device__ __forceinline__ bool fuse_block(const FuseMap& m, int& bx, int& by)
     return bx < m.gx && by < m.gy;
 }
 
-inline long long fuse_blocks(int nx, int ny, int inner)
-{
-    return (long long)((nx + inner - 1) / inner) * ((ny + inner - 1) / inner);
-}
-
-// Regions of a box, E x E nodes with a ring of H.
-enum FuseRegions { kRegions24x8, kRegions32x8, kRegions32x6, kRegions32x4 };
-
-// Choice of region and placement, measured on MI355X on boxes from 64^2 to
-// 3000 x 2000 (us per step; before: four steps per launch on 16 x 16 regions,
-// from 256 blocks up on 32 x 32 regions of four nodes per work-item):
-//  * 24 x 24 regions with eight steps where their 8 x 8 blocks are at most one
-//    per CU: FP64 128^2 1.47 -> 1.20, FP32 1.33 -> 1.00, FP16 1.27 -> 0.96.
-//  * 32 x 32 regions have 1024 work-items and, in FP64, 72 KB of LDS: two fit a
-//    CU, 32 wavefronts.  With eight steps the launches of boxes of up to 288
-//    blocks pay their latency half as often: FP64 170^2 1.92 -> 1.43, 256^2
-//    2.05 -> 1.52, 512 x 128 around a cylinder 2.37 -> 1.74; FP32 256^2 1.78 ->
-//    1.24.  On larger boxes the ring of eight is too much arithmetic (300^2,
-//    361 blocks, 2.10, 384^2 2.76, between walls 2.63 and 3.56) and six steps
-//    are better: 2.49 -> 1.77, 3.19 -> 2.50, 3.29 -> 2.10, 3.77 -> 3.10; 1000 x
-//    777 10.5 -> 8.3; then four: 1024^2 13.4 -> 11.3 (FP16 10.8 -> 6.8), 900 x
-//    800 between walls 9.6 (six steps: 9.8).
-// XCD-aware tiles of 4 x 4 blocks for rings of eight and six up to 512 blocks:
-// 256^2 2.04 -> 1.78, 300^2 2.43 -> 2.03; but 512^2, 676 blocks, 4.1 -> 4.7: the
-// padding to whole tiles.
-constexpr int kFuseTile = 4;
-constexpr int kFuseXcdMaxBlocks = 512;
-
-inline FuseRegions fuse_regions(int nx, int ny, bool walls)
-{
-    if (fuse_blocks(nx, ny, 8) <= 256) return kRegions24x8;
-    if (fuse_blocks(nx, ny, 16) <= 288) return kRegions32x8;
-    return fuse_blocks(nx, ny, 20) <= (walls ? 1280 : 2000) ? kRegions32x6 : kRegions32x4;
-}
-
-// Steps per launch.
-inline int fuse_levels(FuseRegions r)
-{
-    return r == kRegions24x8 || r == kRegions32x8 ? 8 : r == kRegions32x6 ? 6 : 4;
-}
-
 // The placement of an nx x ny box in blocks of `inner` x `inner` stored
 // nodes: tiles of tile x tile blocks (0: plain grid), and the launch grid
 // that goes with it.
@@ -118,10 +76,11 @@ inline FuseMap fuse_plan(int nx, int ny, int inner, int tile, dim3* grid)
         *grid = dim3(unsigned(m.gx), unsigned(m.gy), 1);
         return m;
     }
-    m.tw = m.th = tile;
-    m.tiles_x = (m.gx + tile - 1) / tile;
-    m.tiles = m.tiles_x * ((m.gy + tile - 1) / tile);
-    *grid = dim3(unsigned((m.tiles + 7) / 8) * 8u * unsigned(tile * tile), 1, 1);
+    m.tw = tile < m.gx ? tile : m.gx;
+    m.th = tile < m.gy ? tile : m.gy;
+    m.tiles_x = (m.gx + m.tw - 1) / m.tw;
+    m.tiles = m.tiles_x * ((m.gy + m.th - 1) / m.th);
+    *grid = dim3(unsigned((m.tiles + 7) / 8) * 8u * unsigned(m.tw * m.th), 1, 1);
     return m;
 }
 

@@ -151,8 +151,10 @@ struct Impl {
         return eager(c, n);
     }
 
-    // Steps per launch of the strips of a D2Q9 box (0: it does not take them).
-    static int strip_levels(const lbm_ctx* c) { return stream_levels(c->N, sizeof(S), c->walls); }
+    static Route2D route(const lbm_ctx* c)
+    {
+        return route_2d({c->nx, c->ny, int(c->storage), c->walls, c->links != nullptr, c->comp});
+    }
 
     // Strips of kStreamStore stored columns, segments of rows chosen once per
     // context from the kernel's occupancy (stream_rows).
@@ -176,18 +178,13 @@ struct Impl {
         hipLaunchKernelGGL(kernel, grid, c->block, 0, c->stream, src, dst, step_args<typename Store<S>::C>(c), rows);
     }
 
-    static FuseRegions regions(const lbm_ctx* c)
-    {
-        return fuse_regions(c->nx, c->ny, c->walls);
-    }
-
-    // `steps` (2 .. the steps of the box's regions, or strip_levels) steps of a
-    // D2Q9 two-lattice box in one launch: strips on the largest boxes, else
-    // (and for fewer steps) regions; see stream2d.hpp and fused2d.hpp.
+    // `steps` (2 .. r.most) steps of a D2Q9 two-lattice box in one launch: strips
+    // on the largest boxes, else (and for fewer steps) regions; see
+    // stream2d.hpp and fused2d.hpp.
     template <class K>
-    static void step_fused2d(lbm_ctx* c, const S* src, S* dst, int steps)
+    static void step_fused2d(lbm_ctx* c, const Route2D& r, const S* src, S* dst, int steps)
     {
-        if (steps == strip_levels(c)) {
+        if (steps == r.strips) {
             if (steps == 8) {
                 if constexpr (!K::walls && sizeof(S) > 2) step_strips<K, 8>(c, src, dst);
             } else {
@@ -195,7 +192,7 @@ struct Impl {
             }
             return;
         }
-        switch (regions(c)) {
+        switch (launch_regions(r, steps)) {
         case kRegions24x8: return step_regions<K, 24, 8>(c, src, dst, steps, 0);
         case kRegions32x8: return step_regions<K, 32, 8>(c, src, dst, steps, kFuseTile);
         case kRegions32x6: {
@@ -285,35 +282,28 @@ struct Impl {
             }
         }
         if constexpr (L == 0) {
-            // D2Q9, two lattices: launches of up to eight steps.  Where the
-            // current buffer has to follow the parity of the step count, in
-            // pairs of equal launches, and the remainder one step per launch;
-            // a last single step is always a one-step launch.  Boxes in 16-bit storage between walls
-            // on the axes that would take strips are left to the one-step
-            // kernel (2048^2 FP16: 32.8 us per step, strips 34.8 with halfway
-            // and 38.6 with nodal walls; with a mask 40.3 and 33.8).
-            if (!c->aa && !(sizeof(S) == 2 && c->walls && !c->links && c->N >= kStreamMinNodesWalls)) {
+            // D2Q9, two lattices: launches of several steps (route_2d).  Where
+            // the current buffer has to follow the parity of the step count,
+            // in pairs of equal launches, and the remainder one step per
+            // launch; a last single step is always a one-step launch.
+            const Route2D r = route(c);
+            if (!c->aa && r.most) {
                 const auto fuse = [&](int steps) {
                     const S* src = static_cast<const S*>(c->buf[c->cur]);
                     S* dst = static_cast<S*>(c->buf[1 - c->cur]);
-                    dispatch(c, [&](auto k) { step_fused2d<decltype(k)>(c, src, dst, steps); });
+                    dispatch(c, [&](auto k) { step_fused2d<decltype(k)>(c, r, src, dst, steps); });
                     c->cur = 1 - c->cur;
                     c->steps += steps;
                     i += steps;
                 };
-                const int strips = strip_levels(c);
-                const int most = strips ? strips : fuse_levels(regions(c));
-                for (int k = most;; k = kFuseSteps) {
-                    while (n - i >= 2 * k) {
-                        fuse(k);
-                        fuse(k);
-                    }
-                    if (k == kFuseSteps || !c->by_parity) break;
-                }
-                if (!c->by_parity) {
-                    if (n - i >= most) fuse(most);
-                    const int rest = strips ? kFuseSteps : most;
-                    while (n - i >= 2) fuse(n - i < rest ? n - i : rest);
+                if (c->by_parity) {
+                    for (int k = r.most; k >= r.fewest; k = k > kFuseSteps ? kFuseSteps : 0)
+                        while (n - i >= 2 * k) {
+                            fuse(k);
+                            fuse(k);
+                        }
+                } else {
+                    for (int k; (k = next_launch(r, n - i)) > 0;) fuse(k);
                 }
             }
         }

@@ -159,4 +159,204 @@ inline int march_route(const MarchBox& b, int cus)
     return march_gain(b, p, slots) >= march_least_gain(b) ? p.planes : -1;
 }
 
+// ---------------------------------------------------------------------------
+// Several steps per launch of a D2Q9 box: regions in LDS (fused2d.hpp), and
+// strips streamed up the rows of large boxes (stream2d.hpp).
+
+constexpr int kFuseSteps = 4;  // steps that every region can take in a launch
+
+inline long long fuse_blocks(int nx, int ny, int inner)
+{
+    return (long long)((nx + inner - 1) / inner) * ((ny + inner - 1) / inner);
+}
+
+// Regions of a box, E x E nodes with a ring of H.
+enum FuseRegions { kRegions24x8, kRegions32x8, kRegions32x6, kRegions32x4 };
+
+// Choice of region and placement, measured on MI355X on boxes from 64^2 to
+// 3000 x 2000 (us per step; before: four steps per launch on 16 x 16 regions,
+// from 256 blocks up on 32 x 32 regions of four nodes per work-item):
+//  * 24 x 24 regions with eight steps where their 8 x 8 blocks are at most one
+//    per CU: FP64 128^2 1.47 -> 1.20, FP32 1.33 -> 1.00, FP16 1.27 -> 0.96.
+//  * 32 x 32 regions have 1024 work-items and, in FP64, 72 KB of LDS: two fit a
+//    CU, 32 wavefronts.  With eight steps the launches of boxes of up to 288
+//    blocks pay their latency half as often: FP64 170^2 1.92 -> 1.43, 256^2
+//    2.05 -> 1.52, 512 x 128 around a cylinder 2.37 -> 1.74; FP32 256^2 1.78 ->
+//    1.24.  On larger boxes the ring of eight is too much arithmetic (300^2,
+//    361 blocks, 2.10, 384^2 2.76, between walls 2.63 and 3.56) and six steps
+//    are better: 2.49 -> 1.77, 3.19 -> 2.50, 3.29 -> 2.10, 3.77 -> 3.10; 1000 x
+//    777 10.5 -> 8.3; then four: 1024^2 13.4 -> 11.3 (FP16 10.8 -> 6.8), 900 x
+//    800 between walls 9.6 (six steps: 9.8).
+// XCD-aware tiles of 4 x 4 blocks (fewer where the box has fewer) for rings of
+// eight and six up to 512 blocks: 256^2 2.04 -> 1.78, 300^2 2.43 -> 2.03; but
+// 512^2, 676 blocks, 4.1 -> 4.7: the padding to whole tiles.  Padding a column
+// of blocks to tiles of four left three quarters of the workgroups empty and
+// the others on a quarter of the CUs: 1 x 4096 FP64 24.6 us for eight steps,
+// now 10.0; 4096 x 16 between walls 18.3, now 12.7.
+constexpr int kFuseTile = 4;
+constexpr int kFuseXcdMaxBlocks = 512;
+
+inline FuseRegions fuse_regions(int nx, int ny, bool walls)
+{
+    if (fuse_blocks(nx, ny, 8) <= 256) return kRegions24x8;
+    if (fuse_blocks(nx, ny, 16) <= 288) return kRegions32x8;
+    return fuse_blocks(nx, ny, 20) <= (walls ? 1280 : 2000) ? kRegions32x6 : kRegions32x4;
+}
+
+// Steps per launch.
+inline int fuse_levels(FuseRegions r)
+{
+    return r == kRegions24x8 || r == kRegions32x8 ? 8 : r == kRegions32x6 ? 6 : 4;
+}
+
+constexpr int kStreamCols = 256;  // columns per workgroup, one per work-item
+constexpr int kStreamHalo = 16;   // loaded columns on each side of the stored ones
+constexpr int kStreamStore = kStreamCols - 2 * kStreamHalo;  // 224 stored columns
+// Smaller boxes take the regions of fused2d.hpp.  us per step, strips against
+// regions: FP64 1024^2 14.7 / 11.4, 1500 x 1100 17.4 / 17.3, 2048 x 1024 20.5 /
+// 21.7, 2048^2 32.8 / 42.7; FP32 1024^2 8.4 / 7.6, 2048 x 1024 12.6 / 13.3;
+// FP16 1500^2 16.0 / 12.8, 2048^2 23.5 / 23.8.  Between walls (FP64: 218
+// registers instead of 138, two wavefronts per SIMD instead of three) FP64
+// 1500^2 26.3 / 25.5, 2048^2 45.0 / 46.2, FP32 2048^2 27.5 / 31.3.
+constexpr unsigned kStreamMinNodes = 1u << 21;
+constexpr unsigned kStreamMinNodes16 = 1u << 22;     // 16-bit storage
+constexpr unsigned kStreamMinNodesWalls = 3u << 20;  // between walls
+
+// Steps per launch of a box (0: it does not take strips).  Eight steps read
+// and write the state half as often as four, but hold twice the registers
+// (FP64: 234 instead of 138, two wavefronts per SIMD instead of three) and
+// repeat 16 rows per segment instead of 8.  us per step, four against eight:
+// FP64 1500 x 1100 17.7 / 18.0, 2048^2 35.2 / 32.9, 4096^2 120.9 / 101.9;
+// FP32 2048^2 20.0 / 19.8, 4096^2 67.0 / 53.6; FP16 (bound by instructions)
+// 4096^2 72.8 / 74.8.  Between walls 256 registers would not hold eight.
+inline int stream_levels(unsigned nodes, size_t storage_bytes, bool walls)
+{
+    if (nodes < (walls ? kStreamMinNodesWalls : storage_bytes == 2 ? kStreamMinNodes16 : kStreamMinNodes)) return 0;
+    if (walls || storage_bytes == 2) return 4;
+    return nodes >= (storage_bytes == 8 ? 1u << 22 : 1u << 23) ? 8 : 4;
+}
+
+// A box as the rule sees it; storage as in lbm_storage.
+struct Box2D {
+    int nx, ny;
+    int storage;       // 0 FP64, 1 FP32, 2 FP16, 3 BF16, 4 e4m11
+    bool walls, mask;  // walls: on an axis or of a mask
+    bool comp;         // compressible equilibrium
+};
+
+struct Route2D {
+    int strips;           // steps per launch of strips (0: regions only)
+    FuseRegions regions;  // for the other launches
+    int most, fewest;     // steps per launch (most 0: one-step launches only)
+    bool fours;           // six-step regions: up to four steps on regions of four
+};
+
+// Measured on boxes from 16^2 to 2900^2, 4096 x 1 .. 1024, 1 .. 32 x 4096, 65000 x
+// 3 and x 16, in five storages, periodic, between walls and with masks,
+// against one-step launches (us per step, one-step / several).
+//  * At most one block per CU (24 x 24 and 32 x 32 regions of eight steps): two
+//    steps and more in one launch are never slower, mostly 1.3-3.5 times
+//    faster.
+//  * Larger boxes of which the blocks store less than half (65000 x 3 between
+//    walls: 576-node blocks with 72 stored nodes): FP64 7.8 / 11.5, FP16 4.1 /
+//    14.5: one step.
+//  * 16-bit storage: the conversions of each step weigh more, and short
+//    launches do not pay (FP16 two steps: 512^2 between walls 5.3 / 6.0, 2048^2
+//    27.0 / 39.4): six-step regions from three steps up (1.05-1.5), other
+//    launches from four.  Between walls on the axes strips lost (2048^2 30.4 /
+//    34.8), and with the compressible model regions of four (1024^2 10.6 /
+//    11.4).
+//  * e4m11: a conversion costs as much as a third of a collision.  Only whole
+//    launches of six-step regions pay (512^2 5.4 / 4.5; between walls up to 512
+//    blocks, 384^2 4.5 / 3.6, 512^2 4.9 / 4.9), and strips of rows that the
+//    row-addressed one-step kernel does not take (2900^2 88.8 / 76.5, but
+//    2048^2 26.8 / 47.2), or from 2^23 nodes up around obstacles (2900^2 102.8 /
+//    86.0, 2048^2 43.4 / 50.8).  Regions of four: 1024^2 9.0 / 12.1, 1448^2 22.2 /
+//    21.9, between walls 22.7 / 24.8.
+//  * FP32 with the compressible model between walls, or with strips of rows of
+//    whole cache lines: two steps alone lost (512^2 6.8 / 7.1, 4096 x 1024 49.6 /
+//    52.5).
+inline Route2D route_2d(const Box2D& b)
+{
+    const unsigned nodes = unsigned(b.nx) * unsigned(b.ny);
+    const size_t bytes = b.storage == 0 ? 8 : b.storage == 1 ? 4 : 2;
+    Route2D r;
+    r.regions = fuse_regions(b.nx, b.ny, b.walls);
+    r.strips = stream_levels(nodes, bytes, b.walls);
+    r.most = r.strips ? r.strips : fuse_levels(r.regions);
+    r.fewest = 2;
+    r.fours = false;
+    if (r.regions == kRegions24x8 || r.regions == kRegions32x8) return r;
+    const Route2D one_step = {0, r.regions, 0, 0, false};
+    const bool six = r.regions == kRegions32x6 && !r.strips, axes_only = b.walls && !b.mask;
+    const int inner = r.regions == kRegions32x6 ? 20 : 24;
+    const long long blocks = fuse_blocks(b.nx, b.ny, inner);
+    r.fours = six && !b.walls;
+    if (!r.strips && 2ll * nodes < blocks * inner * inner) return one_step;
+    if (b.storage == 4) {
+        const bool row_addressed = !b.walls && b.nx >= 64 && b.nx <= 4096 && (b.nx & (b.nx - 1)) == 0;
+        if (b.walls && b.comp) return one_step;
+        if (six ? axes_only && blocks > 512 : !r.strips || axes_only || row_addressed) return one_step;
+        if (r.strips && b.mask && nodes < 1u << 23) return one_step;
+        r.fewest = r.most;
+    } else if (bytes == 2) {
+        if (axes_only && (r.strips || (b.comp && !six))) return one_step;
+        r.fewest = six && !(b.walls && b.comp) ? 3 : 4;
+    } else if (b.storage == 1 && ((b.walls && b.comp) || (r.strips && b.nx % 32 == 0))) {
+        r.fewest = 3;
+    }
+    return r;
+}
+
+// Steps of the next launch when `left` are to be made (0: one-step launches
+// from here on).  Of eight steps a periodic six-step box makes four and four
+// instead of six and two (FP64 512^2 40.0 -> 32.0 us, FP32 700^2 45.9 -> 40.4),
+// and where the rest after a whole launch would be one-step launches, two
+// equal ones (eight steps in 16-bit storage on 28 six-step boxes, in the mean
+// over one-step launches: 6 + 1 + 1 x1.37, 4 + 4 x1.46).
+inline int next_launch(const Route2D& r, int left)
+{
+    if (!r.most || left < r.fewest) return 0;
+    if (left < r.most) return r.strips && left > kFuseSteps ? kFuseSteps : left;
+    const int rest = left - r.most;
+    if (!r.strips && r.regions == kRegions32x6 && r.fewest <= kFuseSteps) {
+        if (r.fours && rest == 2) return kFuseSteps;
+        if (rest > 0 && rest < r.fewest && r.fewest > 2 && left >= 2 * r.fewest) return (left + 1) / 2;
+    }
+    return r.most;
+}
+
+// The regions of a launch of `steps` steps that does not run as strips.  In a
+// periodic six-step box up to four steps take the smaller ring (700^2, four
+// steps: FP64 28.6 -> 25.4 us, FP32 22.3 -> 18.7, FP16 19.9 -> 19.4).
+inline FuseRegions launch_regions(const Route2D& r, int steps)
+{
+    return r.fours && steps <= kFuseSteps ? kRegions32x4 : r.regions;
+}
+
+// Rows per segment for an nx x ny box when the GPU runs `slots` workgroups
+// of the kernel at once.  Every workgroup runs rows + 2 H iterations, so a
+// launch takes about ceil(workgroups / slots) rounds of that many: the rows
+// from 8 to 256 that minimise the product (the fewest among equals).  Long
+// segments re-read fewer rows (8 per segment) but leave part of the last
+// round idle unless the workgroups fill it.  Measured with four levels at 4096^2 FP64 (19
+// strips, 768 slots): 103 rows (760 workgroups, the rule's choice) 135,500-
+// 136,700 MLUPS; 64 rows (1216) 130,400-132,300; 52 (1501) 131,900; 86
+// (912) 121,400; 120 (665) 128,500.
+inline int stream_rows(int nx, int ny, long long slots, int levels)
+{
+    const long long strips = (nx + kStreamStore - 1) / kStreamStore;
+    int best = 8;
+    long long best_cost = -1;
+    for (int rows = 8; rows <= 256; ++rows) {
+        const long long wg = strips * ((ny + rows - 1) / rows);
+        const long long cost = (wg + slots - 1) / slots * (rows + 2 * levels);
+        if (best_cost < 0 || cost < best_cost) {
+            best_cost = cost;
+            best = rows;
+        }
+    }
+    return best;
+}
+
 }  // namespace imexlbm

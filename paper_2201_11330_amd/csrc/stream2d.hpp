@@ -38,58 +38,6 @@
 
 namespace imexlbm {
 
-constexpr int kStreamCols = 256;  // columns per workgroup, one per work-item
-constexpr int kStreamHalo = 16;   // loaded columns on each side of the stored ones
-constexpr int kStreamStore = kStreamCols - 2 * kStreamHalo;  // 224 stored columns
-// Smaller boxes take the regions of fused2d.hpp.  us per step, strips against
-// regions: FP64 1024^2 14.7 / 11.4, 1500 x 1100 17.4 / 17.3, 2048 x 1024 20.5 /
-// 21.7, 2048^2 32.8 / 42.7; FP32 1024^2 8.4 / 7.6, 2048 x 1024 12.6 / 13.3;
-// FP16 1500^2 16.0 / 12.8, 2048^2 23.5 / 23.8.  Between walls (FP64: 218
-// registers instead of 138, two wavefronts per SIMD instead of three) FP64
-// 1500^2 26.3 / 25.5, 2048^2 45.0 / 46.2, FP32 2048^2 27.5 / 31.3.
-constexpr unsigned kStreamMinNodes = 1u << 21;
-constexpr unsigned kStreamMinNodes16 = 1u << 22;     // 16-bit storage
-constexpr unsigned kStreamMinNodesWalls = 3u << 20;  // between walls
-
-// Steps per launch of a box (0: it does not take strips).  Eight steps read
-// and write the state half as often as four, but hold twice the registers
-// (FP64: 234 instead of 138, two wavefronts per SIMD instead of three) and
-// repeat 16 rows per segment instead of 8.  us per step, four against eight:
-// FP64 1500 x 1100 17.7 / 18.0, 2048^2 35.2 / 32.9, 4096^2 120.9 / 101.9;
-// FP32 2048^2 20.0 / 19.8, 4096^2 67.0 / 53.6; FP16 (bound by instructions)
-// 4096^2 72.8 / 74.8.  Between walls 256 registers would not hold eight.
-inline int stream_levels(unsigned nodes, size_t storage_bytes, bool walls)
-{
-    if (nodes < (walls ? kStreamMinNodesWalls : storage_bytes == 2 ? kStreamMinNodes16 : kStreamMinNodes)) return 0;
-    if (walls || storage_bytes == 2) return 4;
-    return nodes >= (storage_bytes == 8 ? 1u << 22 : 1u << 23) ? 8 : 4;
-}
-
-// Rows per segment for an nx x ny box when the GPU runs `slots` workgroups
-// of the kernel at once.  Every workgroup runs rows + 2 H iterations, so a
-// launch takes about ceil(workgroups / slots) rounds of that many: the rows
-// from 8 to 256 that minimise the product (the fewest among equals).  Long
-// segments re-read fewer rows (8 per segment) but leave part of the last
-// round idle unless the workgroups fill it.  Measured with four levels at 4096^2 FP64 (19
-// strips, 768 slots): 103 rows (760 workgroups, the rule's choice) 135,500-
-// 136,700 MLUPS; 64 rows (1216) 130,400-132,300; 52 (1501) 131,900; 86
-// (912) 121,400; 120 (665) 128,500.
-inline int stream_rows(int nx, int ny, long long slots, int levels)
-{
-    const long long strips = (nx + kStreamStore - 1) / kStreamStore;
-    int best = 8;
-    long long best_cost = -1;
-    for (int rows = 8; rows <= 256; ++rows) {
-        const long long wg = strips * ((ny + rows - 1) / rows);
-        const long long cost = (wg + slots - 1) / slots * (rows + 2 * levels);
-        if (best_cost < 0 || cost < best_cost) {
-            best_cost = cost;
-            best = rows;
-        }
-    }
-    return best;
-}
-
 // Lane i receives v of lane i - 1 (SHIFT = 0x138, wave_shr:1) or of lane
 // i + 1 (SHIFT = 0x130, wave_shl:1); the edge lane, which is overwritten or
 // not used, receives 0 (keeping its own value would cost a move first).

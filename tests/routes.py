@@ -35,3 +35,24 @@ def march(lattice, dims, storage, bc=(0, 0, 0), mask=False, comp=False):
                                                     + (bool(mask), bool(comp), CUS))
     planes = ask([q])[0][0]
     return planes if planes > 0 else None
+
+
+STORAGE = {"f64": 0, "f32": 1, "f16": 2, "bf16": 3, "e4m11": 4}
+REGIONS = ("24x8", "32x8", "32x6", "32x4")  # edge x most steps
+
+
+def boxes_2d(questions):
+    """Launches of D2Q9 two-lattice boxes, one per question (dims, storage, walls,
+    mask, comp, steps): a list of (steps, "strips" | "24x8" | ... | "one")."""
+    lines = ["2d %d %d %d %d %d %d %d" % (dims[0], dims[1], STORAGE[storage], bool(walls or mask), bool(mask),
+                                          bool(comp), steps)
+             for dims, storage, walls, mask, comp, steps in questions]
+    out = []
+    for row in ask(lines):
+        launches = list(zip(row[4::2], row[5::2]))
+        out.append([(k, "one" if k == 1 else "strips" if r < 0 else REGIONS[r]) for k, r in launches])
+    return out
+
+
+def box_2d(dims, storage, walls=False, mask=False, comp=False, steps=48):
+    return boxes_2d([(dims, storage, walls, mask, comp, steps)])[0]
