@@ -85,6 +85,10 @@ struct lbm_ctx {
     double* d_partials = nullptr;  // kReduceBlocks * 5 + 4 doubles
     double* h_result = nullptr;    // 4 doubles, pinned
 
+    // Arguments of the collision in FP64 and FP32, formed once.
+    imexlbm::CollideArgs<double> collide64;
+    imexlbm::CollideArgs<float> collide32;
+
     int bx_shift = 8;
     dim3 grid, block;
     // Periodic FP64 two-lattice steps with two nodes per work-item (even nx).
@@ -177,9 +181,8 @@ inline StepArgs<C> step_args(const lbm_ctx* c)
     p.g = dims_of(c);
     p.bx_shift = c->bx_shift;
     p.xcd_rows = 0;  // launches on grid_xcd set it
-    p.c = c->lattice == LBM_D2Q9    ? collide_args<0, C>(c->omega, c->F)
-          : c->lattice == LBM_D3Q19 ? collide_args<1, C>(c->omega, c->F)
-                                    : collide_args<2, C>(c->omega, c->F);
+    if constexpr (std::is_same_v<C, double>) p.c = c->collide64;
+    else p.c = c->collide32;
     return p;
 }
 

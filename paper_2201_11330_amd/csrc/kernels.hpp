@@ -362,7 +362,6 @@ __device__ __forceinline__ S get(const S* p)
 //   u = (sum e f + F/2)/rho,  feq_a = w_a rho (1 + 3 e_a.u + 4.5 (e_a.u)^2 - 1.5 u.u).
 // On deviations (DEV) sum g = rho - 1, and feq_a - w_a =
 // w_a (rho - 1 + rho (3 e_a.u + 4.5 (e_a.u)^2 - 1.5 u.u)).
-
 //
 // In FP64 the force term is added per pair of opposite directions (a, abar):
 // with G = 3 (1 - omega/2) w_a e_a.F, formed once on the host,
@@ -377,40 +376,62 @@ template <class C>
 struct CollideArgs {
     C omega;
     C F[3];
-    C k3, k9;    // 3 (1 - omega/2), 9 (1 - omega/2)
-    C push[13];  // G of a = 0 .. Q/2 - 1
-    C w[4];      // w by |e|^2
-    C c3, c45;   // 3, 4.5
+    C k3, k9;  // 3 (1 - omega/2), 9 (1 - omega/2)
 };
 
-// A constant of the collision.  FP64 instructions take no 64-bit literal:
-// written as literals the weights and factors cost a move each time they are
-// used (36 of the 190 vector instructions of a D3Q19 collision, 18 of 87 for
-// D2Q9), as arguments they are read from scalar registers.  FP32 instructions
-// hold them as literals.
-template <class C>
-__device__ __forceinline__ C constant(C arg, double literal)
+// FP64 instructions take no 64-bit literal: written as literals the weights
+// and factors cost a move each time they are used (36 of the 190 vector
+// instructions of a D3Q19 collision, 18 of 87 for D2Q9), as arguments they
+// are read from scalar registers.  FP32 instructions hold them as literals,
+// and the arguments stay short.
+template <>
+struct CollideArgs<double> {
+    double omega;
+    double F[3];
+    double k3, k9;
+    double push[13];  // G of a = 0 .. Q/2 - 1
+    double w[4];      // w by |e|^2
+    double c3, c45;   // 3, 4.5
+};
+
+// The weight w of the directions with |e|^2 = N2, and the factors 3 and 4.5.
+template <int N2, class C>
+__device__ __forceinline__ C weight(const CollideArgs<C>& p, double w)
 {
-    if constexpr (std::is_same_v<C, double>) return arg;
-    else return C(literal);
+    if constexpr (std::is_same_v<C, double>) return p.w[N2];
+    else return C(w);
+}
+template <class C>
+__device__ __forceinline__ C three(const CollideArgs<C>& p)
+{
+    if constexpr (std::is_same_v<C, double>) return p.c3;
+    else return C(3.0);
+}
+template <class C>
+__device__ __forceinline__ C four_and_half(const CollideArgs<C>& p)
+{
+    if constexpr (std::is_same_v<C, double>) return p.c45;
+    else return C(4.5);
 }
 
 // The arguments of lattice L.
 template <int L, class C>
 CollideArgs<C> collide_args(double omega, const double (&F)[3])
 {
-    constexpr auto& LT = kLattice<L>;
     CollideArgs<C> p{};
     p.omega = C(omega);
     for (int d = 0; d < 3; ++d) p.F[d] = C(F[d]);
     const double half = 1.0 - 0.5 * omega;
     p.k3 = C(3.0 * half);
     p.k9 = C(9.0 * half);
-    for (int n = 0; n <= Lattice<L>::kMaxNorm2; ++n) p.w[n] = C(Lattice<L>::weight(n));
-    p.c3 = C(3.0);
-    p.c45 = C(4.5);
-    for (int a = 0; a < Lattice<L>::Q / 2; ++a)
-        p.push[a] = C(3.0 * half * LT.w[a] * (LT.e[a][0] * F[0] + LT.e[a][1] * F[1] + LT.e[a][2] * F[2]));
+    if constexpr (std::is_same_v<C, double>) {
+        constexpr auto& LT = kLattice<L>;
+        for (int n = 0; n <= Lattice<L>::kMaxNorm2; ++n) p.w[n] = Lattice<L>::weight(n);
+        p.c3 = 3.0;
+        p.c45 = 4.5;
+        for (int a = 0; a < Lattice<L>::Q / 2; ++a)
+            p.push[a] = 3.0 * half * LT.w[a] * (LT.e[a][0] * F[0] + LT.e[a][1] * F[1] + LT.e[a][2] * F[2]);
+    }
     return p;
 }
 
@@ -465,9 +486,9 @@ __device__ __forceinline__ void collide(C (&f)[Lattice<L>::Q], const CollideArgs
     static_for<Lattice<L>::Q>([&](auto ac) {
         constexpr int a = decltype(ac)::value;
         constexpr int ex = kLattice<L>.e[a][0], ey = kLattice<L>.e[a][1], ez = kLattice<L>.e[a][2];
-        const C w = constant<C>(p.w[ex * ex + ey * ey + ez * ez], kLattice<L>.w[a]);
+        const C w = weight<ex * ex + ey * ey + ez * ez>(p, kLattice<L>.w[a]);
         const C edu = eterm<ex>(m.ux) + eterm<ey>(m.uy) + eterm<ez>(m.uz);
-        const C feq = w * (base + (COMP ? m.rf * edu : edu) * (constant<C>(p.c3, 3.0) + constant<C>(p.c45, 4.5) * edu));
+        const C feq = w * (base + (COMP ? m.rf * edu : edu) * (three(p) + four_and_half(p) * edu));
         C fs = f[a] + p.omega * (feq - f[a]);
         if constexpr (FORCE && !kPairForce) {
             const C eF = eterm<ex>(p.F[0]) + eterm<ey>(p.F[1]) + eterm<ez>(p.F[2]);
@@ -480,11 +501,11 @@ __device__ __forceinline__ void collide(C (&f)[Lattice<L>::Q], const CollideArgs
             constexpr int a = decltype(ac)::value, abar = Lattice<L>::opp(a);
             constexpr int ex = kLattice<L>.e[a][0], ey = kLattice<L>.e[a][1], ez = kLattice<L>.e[a][2];
             const C edu = eterm<ex>(m.ux) + eterm<ey>(m.uy) + eterm<ez>(m.uz);
-            const C both = constant<C>(p.c3, 3.0) * edu * p.push[a] - constant<C>(p.w[ex * ex + ey * ey + ez * ez], kLattice<L>.w[a]) * (p.k3 * uF);
+            const C both = three(p) * edu * p.push[a] - weight<ex * ex + ey * ey + ez * ez>(p, kLattice<L>.w[a]) * (p.k3 * uF);
             f[a] += both + p.push[a];
             f[abar] += both - p.push[a];
         });
-        f[Lattice<L>::Q / 2] -= constant<C>(p.w[0], kLattice<L>.w[Lattice<L>::Q / 2]) * (p.k3 * uF);
+        f[Lattice<L>::Q / 2] -= weight<0>(p, kLattice<L>.w[Lattice<L>::Q / 2]) * (p.k3 * uF);
     }
 }
 

@@ -246,6 +246,10 @@ lbm_status lbm_create(lbm_ctx** out, lbm_lattice lattice, int nx, int ny, int nz
         c->F[d] = F[d];
         c->bc[d] = b[d];
     }
+    c->collide64 = lattice == LBM_D2Q9    ? collide_args<0, double>(c->omega, c->F)
+                   : lattice == LBM_D3Q19 ? collide_args<1, double>(c->omega, c->F)
+                                          : collide_args<2, double>(c->omega, c->F);
+    c->collide32 = collide_args<0, float>(c->omega, c->F);  // the same for every lattice
     c->storage = storage;
     c->ops = lattice == LBM_D2Q9 ? ops_d2q9(storage)
              : (lattice == LBM_D3Q19 ? ops_d3q19(storage) : ops_d3q27(storage));
