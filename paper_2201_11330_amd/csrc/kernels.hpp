@@ -364,7 +364,8 @@ __device__ __forceinline__ S get(const S* p)
 // w_a (rho - 1 + rho (3 e_a.u + 4.5 (e_a.u)^2 - 1.5 u.u)).
 //
 // In FP64 the force term is added per pair of opposite directions (a, abar):
-// with G = 3 (1 - omega/2) w_a e_a.F, formed once on the host,
+// with G = 3 (1 - omega/2) w_a e_a.F, formed once on the host for the launches of
+// several steps (rounded as ((3 (1 - omega/2)) w_a) (e_a.F) in both places),
 //   f*_a += (3 e_a.u G - 3 (1 - omega/2) w_a u.F) + G,
 //   f*_abar += (3 e_a.u G - 3 (1 - omega/2) w_a u.F) - G,
 // six operations per pair; the term as it stands takes five per direction and
@@ -383,7 +384,10 @@ struct CollideArgs {
 // and factors cost a move each time they are used (36 of the 190 vector
 // instructions of a D3Q19 collision, 18 of 87 for D2Q9), as arguments they
 // are read from scalar registers.  FP32 instructions hold them as literals,
-// and the arguments stay short.
+// and the arguments stay short.  So do the one-step kernels (LITERALS), which
+// are not bound by instructions, and form G from F: with the force term and
+// walls 41 of the scalar registers were spilled (FP64 24^3 between solid end
+// planes ran at x0.965 of the rate without these arguments, now x1.008).
 template <>
 struct CollideArgs<double> {
     double omega;
@@ -395,22 +399,22 @@ struct CollideArgs<double> {
 };
 
 // The weight w of the directions with |e|^2 = N2, and the factors 3 and 4.5.
-template <int N2, class C>
+template <int N2, bool LITERALS, class C>
 __device__ __forceinline__ C weight(const CollideArgs<C>& p, double w)
 {
-    if constexpr (std::is_same_v<C, double>) return p.w[N2];
+    if constexpr (std::is_same_v<C, double> && !LITERALS) return p.w[N2];
     else return C(w);
 }
-template <class C>
+template <bool LITERALS, class C>
 __device__ __forceinline__ C three(const CollideArgs<C>& p)
 {
-    if constexpr (std::is_same_v<C, double>) return p.c3;
+    if constexpr (std::is_same_v<C, double> && !LITERALS) return p.c3;
     else return C(3.0);
 }
-template <class C>
+template <bool LITERALS, class C>
 __device__ __forceinline__ C four_and_half(const CollideArgs<C>& p)
 {
-    if constexpr (std::is_same_v<C, double>) return p.c45;
+    if constexpr (std::is_same_v<C, double> && !LITERALS) return p.c45;
     else return C(4.5);
 }
 
@@ -474,7 +478,7 @@ __device__ __forceinline__ Moments<L, C> node_moments(const C (&f)[Lattice<L>::Q
     return m;
 }
 
-template <int L, class C, bool FORCE, bool COMP = false, bool DEV = false>
+template <int L, class C, bool FORCE, bool COMP = false, bool DEV = false, bool LITERALS = false>
 __device__ __forceinline__ void collide(C (&f)[Lattice<L>::Q], const CollideArgs<C>& p)
 {
     constexpr bool kPairForce = std::is_same_v<C, double>;
@@ -486,9 +490,9 @@ __device__ __forceinline__ void collide(C (&f)[Lattice<L>::Q], const CollideArgs
     static_for<Lattice<L>::Q>([&](auto ac) {
         constexpr int a = decltype(ac)::value;
         constexpr int ex = kLattice<L>.e[a][0], ey = kLattice<L>.e[a][1], ez = kLattice<L>.e[a][2];
-        const C w = weight<ex * ex + ey * ey + ez * ez>(p, kLattice<L>.w[a]);
+        const C w = weight<ex * ex + ey * ey + ez * ez, LITERALS>(p, kLattice<L>.w[a]);
         const C edu = eterm<ex>(m.ux) + eterm<ey>(m.uy) + eterm<ez>(m.uz);
-        const C feq = w * (base + (COMP ? m.rf * edu : edu) * (three(p) + four_and_half(p) * edu));
+        const C feq = w * (base + (COMP ? m.rf * edu : edu) * (three<LITERALS>(p) + four_and_half<LITERALS>(p) * edu));
         C fs = f[a] + p.omega * (feq - f[a]);
         if constexpr (FORCE && !kPairForce) {
             const C eF = eterm<ex>(p.F[0]) + eterm<ey>(p.F[1]) + eterm<ez>(p.F[2]);
@@ -501,11 +505,20 @@ __device__ __forceinline__ void collide(C (&f)[Lattice<L>::Q], const CollideArgs
             constexpr int a = decltype(ac)::value, abar = Lattice<L>::opp(a);
             constexpr int ex = kLattice<L>.e[a][0], ey = kLattice<L>.e[a][1], ez = kLattice<L>.e[a][2];
             const C edu = eterm<ex>(m.ux) + eterm<ey>(m.uy) + eterm<ez>(m.uz);
-            const C both = three(p) * edu * p.push[a] - weight<ex * ex + ey * ey + ez * ez>(p, kLattice<L>.w[a]) * (p.k3 * uF);
-            f[a] += both + p.push[a];
-            f[abar] += both - p.push[a];
+            const C w = weight<ex * ex + ey * ey + ez * ez, LITERALS>(p, kLattice<L>.w[a]);
+            C push;
+            if constexpr (LITERALS) {
+                const C kw = p.k3 * w;  // statements of their own: nothing is contracted
+                const C eF = eterm<ex>(p.F[0]) + eterm<ey>(p.F[1]) + eterm<ez>(p.F[2]);
+                push = kw * eF;
+            } else {
+                push = p.push[a];
+            }
+            const C both = three<LITERALS>(p) * edu * push - w * (p.k3 * uF);
+            f[a] += both + push;
+            f[abar] += both - push;
         });
-        f[Lattice<L>::Q / 2] -= weight<0>(p, kLattice<L>.w[Lattice<L>::Q / 2]) * (p.k3 * uF);
+        f[Lattice<L>::Q / 2] -= weight<0, LITERALS>(p, kLattice<L>.w[Lattice<L>::Q / 2]) * (p.k3 * uF);
     }
 }
 
@@ -610,7 +623,7 @@ __global__ LBM_STEP_BOUNDS void k_step_ab(const S* __restrict__ src, S* __restri
         f[a] = Store<S>::load(get<NT && aligned>(ptr));
     });
     if constexpr (WALLS) nodal_fill<L>(p.g, x, y, z, f);
-    collide<L, C, FORCE, COMP, Store<S>::kDeviation>(f, p.c);
+    collide<L, C, FORCE, COMP, Store<S>::kDeviation, true>(f, p.c);
     if constexpr (NT) {
         const auto ws = WaveStores<S>::template make<Q>(dst, own, p.g);
         static_for<Q>([&](auto ac) {
@@ -670,7 +683,7 @@ __global__ LBM_STEP_BOUNDS void k_step_ab_rows(const S* __restrict__ src, S* __r
         const unsigned off = (unsigned(a) << TS) * unsigned(sizeof(S)) + (ex == 0 ? bx : (ex == 1 ? bxm : bxp));
         f[a] = Store<S>::load(get<NT && ex == 0>(reinterpret_cast<const S*>(run + off)));
     });
-    collide<L, C, FORCE, COMP, Store<S>::kDeviation>(f, p.c);
+    collide<L, C, FORCE, COMP, Store<S>::kDeviation, true>(f, p.c);
     const unsigned r = unsigned(g.nx) * (unsigned(y) + unsigned(g.ny) * unsigned(z));
     S* run = dst + ((size_t(r >> TS) * Q) << TS) + (r & mask);  // own row, direction 0
     if constexpr (NT) {
@@ -784,8 +797,8 @@ __global__ LBM_STEP_BOUNDS void k_step_ab_pairs(const double* __restrict__ src,
         }
     });
     if (!active) return;
-    collide<L, double, FORCE, COMP, false>(f0, p.c);
-    collide<L, double, FORCE, COMP, false>(f1, p.c);
+    collide<L, double, FORCE, COMP, false, true>(f0, p.c);
+    collide<L, double, FORCE, COMP, false, true>(f1, p.c);
     const unsigned own = unsigned(x0) + unsigned(g.nx) * (unsigned(y) + unsigned(g.ny) * unsigned(z));
     const auto ws = WaveStores<double>::make<Q>(dst, own, g);
     static_for<Q>([&](auto ac) {
@@ -827,8 +840,8 @@ __global__ LBM_STEP_BOUNDS void k_step_aa_even_pairs(double* __restrict__ A, Ste
         f0[a] = v.lo;
         f1[a] = v.hi;
     });
-    collide<L, double, FORCE, COMP, false>(f0, p.c);
-    collide<L, double, FORCE, COMP, false>(f1, p.c);
+    collide<L, double, FORCE, COMP, false, true>(f0, p.c);
+    collide<L, double, FORCE, COMP, false, true>(f1, p.c);
     const auto ws = WaveStores<double>::make<Q>(A, own, g);
     static_for<Q>([&](auto ac) {
         constexpr int a = decltype(ac)::value;
@@ -883,8 +896,8 @@ __global__ LBM_STEP_BOUNDS void k_step_aa_odd_pairs(double* __restrict__ A, Step
             f1[a] = last;
         }
     });
-    collide<L, double, FORCE, COMP, false>(f0, p.c);
-    collide<L, double, FORCE, COMP, false>(f1, p.c);
+    collide<L, double, FORCE, COMP, false, true>(f0, p.c);
+    collide<L, double, FORCE, COMP, false, true>(f1, p.c);
     // f*_a(x) goes to slot a of x + e_a, in the row read for abar.
     static_for<Q>([&](auto ac) {
         constexpr int a = decltype(ac)::value;
@@ -928,7 +941,7 @@ __global__ LBM_STEP_BOUNDS void k_step_aa_even(S* __restrict__ A,
         f[a] = Store<S>::load(get<NT>(A + slot<Q>(a, own, TS)));
     });
     if constexpr (WALLS) nodal_fill<L>(p.g, x, y, z, f);
-    collide<L, C, FORCE, COMP, Store<S>::kDeviation>(f, p.c);
+    collide<L, C, FORCE, COMP, Store<S>::kDeviation, true>(f, p.c);
     if constexpr (NT) {
         const auto ws = WaveStores<S>::template make<Q>(A, own, p.g);
         static_for<Q>([&](auto ac) {
@@ -972,7 +985,7 @@ __global__ LBM_STEP_BOUNDS void k_step_aa_odd(S* __restrict__ A,
         f[a] = Store<S>::load(get<NT && kLattice<L>.e[a][0] == 0>(A + off[a]));
     });
     if constexpr (WALLS) nodal_fill<L>(p.g, x, y, z, f);
-    collide<L, C, FORCE, COMP, Store<S>::kDeviation>(f, p.c);
+    collide<L, C, FORCE, COMP, Store<S>::kDeviation, true>(f, p.c);
     static_for<Q>([&](auto ac) {
         constexpr int a = decltype(ac)::value;
         put<NT>(A + off[Lattice<L>::opp(a)], Store<S>::save(f[a]));
