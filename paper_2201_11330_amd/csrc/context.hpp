@@ -170,6 +170,7 @@ inline IoArgs io_args(const lbm_ctx* c)
     p.bx_shift = c->bx_shift;
     p.mode = state_mode(c);
     p.comp = c->comp ? 1 : 0;
+    p.by_rows = 0;
     for (int d = 0; d < 3; ++d) p.F[d] = c->F[d];
     return p;
 }

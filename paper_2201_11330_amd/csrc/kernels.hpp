@@ -1002,6 +1002,7 @@ struct IoArgs {
     int bx_shift;
     int mode;  // GatherMode of the stored state
     int comp;  // compressible model: u = (sum e f + F/2)/rho
+    int by_rows;  // work-items on the grid of node_of_item, else in node order
     double F[3];
 };
 
@@ -1109,17 +1110,28 @@ __device__ __forceinline__ void gather_node(const S* __restrict__ A, const IoArg
     });
 }
 
-// State import, export and moments: one node per work-item in node order, so
+// State import, export and moments: one node per work-item, in node order, so
 // that no lanes idle past the end of a row (192 x 160 x 144 FP64: export 284 ->
-// 254 us, import the same).  Four nodes per work-item, 256 apart, were slower
-// (256^3 import 640 -> 656 us).
-__device__ __forceinline__ bool node_in_order(const Dims& g, unsigned& n, int& x, int& y, int& z)
+// 254 us, import the same), or by rows where few would (Impl::read_args,
+// Impl::import).  Four nodes per work-item, 256 apart, were slower (256^3 import
+// 640 -> 656 us).
+__device__ __forceinline__ bool io_node(const IoArgs& p, unsigned& n, int& x, int& y, int& z)
 {
+    if (p.by_rows) {
+        if (!node_of_item(p.g, p.bx_shift, x, y, z)) return false;
+        n = node_index(p.g, x, y, z);
+        return true;
+    }
     n = blockIdx.x * 256u + threadIdx.x;
-    if (n >= g.N) return false;
-    split_node(g, n, x, y, z);
+    if (n >= p.g.N) return false;
+    split_node(p.g, n, x, y, z);
     return true;
 }
+
+// Initial states between walls in FP64: one row per workgroup where that
+// leaves few lanes idle (Impl::import).
+template <int L, class S, bool WALLS>
+inline constexpr bool kImportByRows = L != 0 && std::is_same_v<S, double> && WALLS;
 
 // f^n from equilibrium (rho, u) plus optional noise, or from f (when f is
 // non-null), written into the stored state.  Deviation storages store f - w.
@@ -1129,34 +1141,34 @@ __global__ __launch_bounds__(256) void k_import(S* __restrict__ A, const double*
                                                 const double* __restrict__ u,
                                                 const double* __restrict__ noise, IoArgs p)
 {
+    constexpr int Q = Lattice<L>::Q;
     const unsigned N = p.g.N;
     unsigned n;
     int x, y, z;
-    if (!node_in_order(p.g, n, x, y, z)) return;
+    if (!io_node(p, n, x, y, z)) return;
     if (WALLS && is_solid(p.g, x, y, z)) return;
-    const auto import_all = [&](auto&& value) {
-        const NodeSlots<L, WALLS> at(p, x, y, z, n);
-        static_for<Lattice<L>::Q>([&](auto ac) {
-            constexpr int a = decltype(ac)::value;
-            double v = value(ac);
-            if constexpr (Store<S>::kDeviation) v -= kLattice<L>.w[a];
-            A[at.template slot_of<a>(p)] = Store<S>::save(typename Store<S>::C(v));
-        });
+    const auto stored = [&](auto ac, double v) {
+        if constexpr (Store<S>::kDeviation) v -= kLattice<L>.w[decltype(ac)::value];
+        return Store<S>::save(typename Store<S>::C(v));
     };
     if (f) {
         // All loads before the stores: D3Q27 174 x 160 x 48 FP16 75.6 -> 71.1 us.
-        double fn[Lattice<L>::Q];
-        static_for<Lattice<L>::Q>([&](auto ac) {
+        double fn[Q];
+        static_for<Q>([&](auto ac) {
             constexpr int a = decltype(ac)::value;
             fn[a] = f[size_t(a) * N + n];
         });
-        import_all([&](auto ac) { return fn[decltype(ac)::value]; });
+        const NodeSlots<L, WALLS> at(p, x, y, z, n);
+        static_for<Q>([&](auto ac) {
+            constexpr int a = decltype(ac)::value;
+            A[at.template slot_of<a>(p)] = stored(ac, fn[a]);
+        });
         return;
     }
     const double r = rho[n];
     const double ux = u[n], uy = u[size_t(N) + n], uz = kDim<L> == 3 ? u[2 * size_t(N) + n] : 0.0;
     const double usq = ux * ux + uy * uy + uz * uz;
-    import_all([&](auto ac) {
+    const auto value = [&](auto ac) {
         constexpr int a = decltype(ac)::value;
         constexpr auto& LT = kLattice<L>;
         const double edu = eterm<LT.e[a][0]>(ux) + eterm<LT.e[a][1]>(uy) + eterm<LT.e[a][2]>(uz);
@@ -1164,7 +1176,32 @@ __global__ __launch_bounds__(256) void k_import(S* __restrict__ A, const double*
         double v = LT.w[a] * (r + rq * (3.0 * edu + 4.5 * edu * edu - 1.5 * usq));
         if (noise) v += noise[size_t(a) * N + n];
         return v;
-    });
+    };
+    if constexpr (kImportByRows<L, S, WALLS>) {
+        // All values before the stores, places by gather_offset: D3Q19 256^3
+        // between walls 594 -> 546 us.
+        unsigned idx[Q];
+        bool wall[Q];
+        link_nodes<L, WALLS, -1>(p.g, x, y, z, idx, wall);
+        double fn[Q];
+        static_for<Q>([&](auto ac) { fn[decltype(ac)::value] = value(ac); });
+        static_for<Q>([&](auto ac) {
+            constexpr int a = decltype(ac)::value;
+            A[gather_offset<L>(p.mode, a, n, idx[a], wall[a], p.g.S)] = stored(ac, fn[a]);
+        });
+    } else {
+        // FP32 and 16 bits: the places before the values (the empty asm keeps
+        // them there), so that the stores follow each other closely: D3Q19
+        // FP16 256^3 256 -> 224 us.
+        const NodeSlots<L, WALLS> at(p, x, y, z, n);
+        size_t places[Q];
+        static_for<Q>([&](auto ac) {
+            constexpr int a = decltype(ac)::value;
+            places[a] = at.template slot_of<a>(p);
+            if constexpr (sizeof(S) < 8) asm volatile("" : "+v"(places[a]));
+        });
+        static_for<Q>([&](auto ac) { A[places[decltype(ac)::value]] = stored(ac, value(ac)); });
+    }
 }
 
 // rho, u of f^n as the model defines them, and the sum of the stored values
@@ -1198,7 +1235,7 @@ __global__ __launch_bounds__(256) void k_export(const S* __restrict__ A, double*
     const unsigned N = p.g.N;
     unsigned n;
     int x, y, z;
-    if (!node_in_order(p.g, n, x, y, z)) return;
+    if (!io_node(p, n, x, y, z)) return;
     if (WALLS && is_solid(p.g, x, y, z)) {
         for (int a = 0; a < Lattice<L>::Q; ++a) f[size_t(a) * N + n] = 0.0;
         return;
@@ -1226,7 +1263,7 @@ __global__ __launch_bounds__(256) void k_moments(const S* __restrict__ A, O* __r
     const unsigned N = p.g.N;
     unsigned own;
     int x, y, z;
-    if (!node_in_order(p.g, own, x, y, z)) return;
+    if (!io_node(p, own, x, y, z)) return;
     if (WALLS && is_solid(p.g, x, y, z)) {
         if (rho) rho[own] = O(0);
         if (u) u[own] = u[size_t(N) + own] = u[2 * size_t(N) + own] = O(0);
