@@ -82,7 +82,7 @@ struct lbm_ctx {
     long long steps = 0;
 
     unsigned* links = nullptr;     // per-node link bits of a solid mask (lbm_set_solid)
-    double* d_partials = nullptr;  // kReduceBlocks * 5 + 4 doubles
+    double* d_partials = nullptr;  // kReduceBlocks * 5 doubles
     double* h_result = nullptr;    // 4 doubles, pinned
 
     // Arguments of the collision in FP64 and FP32, formed once.

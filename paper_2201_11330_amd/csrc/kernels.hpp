@@ -1192,7 +1192,7 @@ __global__ __launch_bounds__(256) void k_import(S* __restrict__ A, const double*
     } else {
         // FP32 and 16 bits: the places before the values (the empty asm keeps
         // them there), so that the stores follow each other closely: D3Q19
-        // FP16 256^3 256 -> 224 us.
+        // FP16 256^3 258 -> 240 us.
         const NodeSlots<L, WALLS> at(p, x, y, z, n);
         size_t places[Q];
         static_for<Q>([&](auto ac) {

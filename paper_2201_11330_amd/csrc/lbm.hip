@@ -156,8 +156,9 @@ lbm_status check_device_ptr(const void* p, const char* name, bool allow_null, si
 
 // Device scratch of lbm_reduce_noalloc: the Monitor's per-workgroup
 // partials (5 doubles for each of the kReduceBlocks workgroups, which stride
-// over the whole box, so every box size fits) and the 4 results.  Each device
-// holds its own copy until the process ends; calls on one device share it.
+// over the whole box, so every box size fits) and 4 results that are copied to
+// a misaligned destination.  Each device holds its own copy until the process
+// ends; calls on one device share it.
 constexpr size_t kScratchDoubles = 5 * size_t(kReduceBlocks) + 4;
 static __device__ __align__(256) double scratch[kScratchDoubles];
 
@@ -290,7 +291,7 @@ lbm_status lbm_bind(lbm_ctx* c, void* buf_a, void* buf_b, void* hip_stream)
         return fail(LBM_EINVAL, "population buffers must be 256-byte aligned");
     int dev = -1;
     LBM_HIP(hipGetDevice(&dev));
-    LBM_HIP(hipMalloc(&c->d_partials, sizeof(double) * (5 * size_t(kReduceBlocks) + 4)));
+    LBM_HIP(hipMalloc(&c->d_partials, sizeof(double) * 5 * kReduceBlocks));
     hipError_t e = hipHostMalloc(reinterpret_cast<void**>(&c->h_result), 4 * sizeof(double), hipHostMallocDefault);
     if (e != hipSuccess) {
         (void)hipFree(c->d_partials);
@@ -388,11 +389,6 @@ lbm_status lbm_reduce_noalloc(lbm_ctx* c, double* result)
 {
     lbm_status st = need_state(c);
     if (st) return st;
-    static_assert(kScratchDoubles >= 5 * size_t(kReduceBlocks) + 4, "scratch too small for the partials");
-    const size_t need = 5 * size_t(kReduceBlocks) + 4;  // the same for every box size
-    if (need > kScratchDoubles)
-        return fail(LBM_EINVAL, "the reduction needs %zu doubles of scratch, the maximum is %zu", need,
-                    kScratchDoubles);
     if ((st = check_device_ptr(result, "result", false, 4 * sizeof(double)))) return st;
     int dev = -1;
     LBM_HIP(hipGetDevice(&dev));
@@ -402,7 +398,13 @@ lbm_status lbm_reduce_noalloc(lbm_ctx* c, double* result)
     double* ptr = nullptr;
     if ((st = scratch_address(dev, &ptr))) return st;
     note_capture(c);
-    return c->ops->reduce(c, ptr, result);
+    // The last kernel writes the results where its stores may: a destination
+    // that is not aligned for them gets a copy.
+    if (reinterpret_cast<uintptr_t>(result) % alignof(double) == 0) return c->ops->reduce(c, ptr, result);
+    double* out = ptr + 5 * size_t(kReduceBlocks);
+    if ((st = c->ops->reduce(c, ptr, out))) return st;
+    LBM_HIP(hipMemcpyAsync(result, out, 4 * sizeof(double), hipMemcpyDeviceToDevice, c->stream));
+    return LBM_OK;
 }
 
 long long lbm_steps_taken(const lbm_ctx* c) { return c ? c->steps : -1; }
