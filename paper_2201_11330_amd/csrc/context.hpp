@@ -122,6 +122,7 @@ namespace imexlbm {
 
 // Operations of one lattice and storage (Impl<L, S> in impl.hpp).
 struct Ops {
+    bool (*multi_step)(lbm_ctx*);  // whether the box takes launches of several steps
     lbm_status (*step)(lbm_ctx*, int n);
     lbm_status (*import)(lbm_ctx*, const double* f, const double* rho, const double* u,
                          const double* noise);

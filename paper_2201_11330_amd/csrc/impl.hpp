@@ -262,6 +262,14 @@ struct Impl {
         return c->march_planes > 0;
     }
 
+    static bool multi_step(lbm_ctx* c)
+    {
+        if (c->aa) return false;
+        if constexpr (L == 0) return route(c).most > 0;
+        else if constexpr (kMarch) return takes_march(c);
+        else return false;
+    }
+
     static lbm_status eager(lbm_ctx* c, int n)
     {
         int i = 0;
@@ -549,7 +557,7 @@ struct Impl {
 
     static const Ops* ops()
     {
-        static const Ops table = {&step, &import, &export_f, &moments, &reduce, &adjoint,
+        static const Ops table = {&multi_step, &step, &import, &export_f, &moments, &reduce, &adjoint,
                                   &build_links, &wall_force, &step_between};
         return &table;
     }

@@ -106,11 +106,11 @@ lbm_status need_state(const lbm_ctx* c)
 // the buffers of the capture, and between replays the caller may take other
 // steps, import a new state or replay other graphs of the context: that works
 // as long as the same step counts, even or odd, always have the same buffer.
-// So from the first captured call on they do.  (The null stream cannot be
-// captured.)
+// So from the first captured call on they do.  (A box that takes one-step
+// launches alone always does, and the null stream cannot be captured.)
 void note_capture(lbm_ctx* c)
 {
-    if (c->aa || c->by_parity || !c->stream) return;
+    if (c->by_parity || !c->stream || !c->ops->multi_step(c)) return;
     hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(c->stream, &status) != hipSuccess) {
         (void)hipGetLastError();
