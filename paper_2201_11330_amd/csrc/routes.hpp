@@ -85,13 +85,31 @@ inline MarchWallKind march_wall_kind(const MarchBox& b)
     return b.bc[1] != 0 || b.bc[2] != 0 ? kMarchWallsYZ : kMarchNoWalls;
 }
 
+// What a node costs the one-step kernels, in units of its bytes at 6.3 TB/s
+// (medians over 2,500 boxes).  Rows of whole cache lines: 1.0, and above 256
+// nodes, where a row takes several workgroups, more the longer the padding of
+// the last one (272 nodes, 512 lanes: FP64 1.27, FP32 1.6).  Other rows: FP64
+// 1.4-1.5 up to 256 nodes and 1.4-1.8 above, FP32 1.6-1.9 and 1.85-2.05; rows of
+// half lines FP64 1.04, FP32 1.1 and up to 1.5.
+inline double one_step_cost(int nx, size_t storage_bytes)
+{
+    int lanes = 1;
+    while (lanes < nx && lanes < 256) lanes *= 2;
+    const double pad = double((nx + lanes - 1) / lanes) * lanes / nx - 1.0;
+    const bool wide = nx > 256;
+    if (storage_bytes == 8) {
+        if (nx % 8 == 0) return (nx % 16 == 0 ? 1.0 : 1.06) + (wide ? 0.3 * pad : 0.0);
+        return 1.38 + (wide ? 0.4 : 0.12) * pad;
+    }
+    if (nx % 32 == 0) return 1.0 + (wide ? 0.65 : 0.05) * pad;
+    if (nx % 16 == 0) return 1.1 + (wide ? 0.5 : 0.05) * pad;
+    return 1.6 + (wide ? 0.25 + 0.15 * pad : 0.0);
+}
+
 // Estimated time of two one-step launches over that of a two-step launch with
 // `slots` workgroups at once, each in units of a row of 64 nodes.
 //   * One step: the fluid nodes (solid end planes are skipped) and about 4 us
-//     of launch at the 6.3 TB/s of those kernels.  Rows that are not whole
-//     cache lines cost 1.2-1.9 x as much there, the more the longer the
-//     padding of their lanes (FP64, ps per node: 128 x 128 x 128 49,
-//     100^3 58, 193 x 127 x 101 67, 257 x 100 x 100 83).
+//     of launch.
 //   * Two steps: every workgroup slot makes planes + 3 iterations per round,
 //     an iteration costs its stored rows and what does not depend on their
 //     number (level 1 next to the tile, barriers, link bits between walls).
@@ -100,40 +118,35 @@ inline MarchWallKind march_wall_kind(const MarchBox& b)
 inline double march_gain(const MarchBox& b, const MarchPlan& p, long long slots)
 {
     const double bytes = 2.0 * (b.lattice == 1 ? 19 : 27) * double(b.storage_bytes);
-    double nodes = double(b.n[0]) * b.n[1] * b.n[2];
+    double nodes = double(b.n[0]) * b.n[1] * b.n[2] * one_step_cost(b.n[0], b.storage_bytes);
     for (int d = 0; d < 3; ++d)
         if (b.bc[d] == 1) nodes *= double(b.n[d] - 2) / b.n[d];
-    int lanes = 1;
-    while (lanes < b.n[0] && lanes < 256) lanes *= 2;
-    const double padded = double((b.n[0] + lanes - 1) / lanes) * lanes / b.n[0];
-    if (size_t(b.n[0]) * b.storage_bytes % 128 != 0) nodes *= 1.1 + 0.25 * (padded - 1.0);
     const double one = nodes / 64 + 4e-6 * 6.3e12 / (64 * bytes);
     const MarchWallKind kind = march_wall_kind(b);
-    const int fixed = kind == kMarchNoWalls ? 6 : kind == kMarchSolids ? 4 : 11;
+    const int fixed = kind == kMarchNoWalls ? 4 : kind == kMarchSolids ? 2 : b.comp ? 14 : 10;
     const long long groups = (long long)p.tiles_x * p.tiles_y * ((b.n[2] + p.planes - 1) / p.planes);
     const double rounds = double((groups + slots - 1) / slots);
     return 2.0 * one / (double(slots) * rounds * (p.planes + 3) * (p.rows + fixed));
 }
 
 // The least march_gain with which two-step launches are taken: per kind of
-// walls and model the smallest value above which at most a handful of about
-// 5,500 boxes (edges of 24-700 nodes, a few rows or planes among them) ran
-// below x0.96 of one-step launches.  On 3,200 other random boxes of edges
-// 16-512 none is slower than one-step launches by more than 5 % and the rule
-// gains x1.16 in the mean, with two steps for all x1.17 and 128 of them slower
-// than that, the faster launch of each box x1.18.  Where it refuses, two-step
-// launches took up to 2.7 times as long (us per step: 512 x 3 x 512
-// compressible between solid end planes 19.2 -> 52.0, 512 x 512 x 4 between
-// solid end planes 29.7 -> 70.3, D3Q27 112^3 around a sphere 98.6 -> 121.8,
-// D3Q19 FP32 160^3 around a sphere 104.9 -> 126.0).  Columns: D3Q19 FP64,
-// D3Q27 FP64, FP32.  Second rows: the compressible model, for which 64
-// registers (FP32) or 128 between walls do not hold what a node keeps.
+// walls and model the smallest value above which few of 9,800 boxes (edges of
+// 24-700 nodes, a few rows or planes among them) ran below x0.95 of one-step
+// launches (30 of them, 619 with two steps for all).  On 3,000 other boxes of
+// random edges the rule gains x1.328 in the mean, two steps for all x1.322, the
+// faster launch of each box x1.331.  Where it refuses, two-step launches took
+// up to 2.7 times as long (us per step: 512 x 3 x 512 compressible between solid
+// end planes 19.2 -> 52.0, 512 x 512 x 4 between solid end planes 29.7 -> 70.3,
+// D3Q27 112^3 around a sphere 98.6 -> 121.8, D3Q19 FP32 160^3 around a sphere
+// 104.9 -> 126.0).  Columns: D3Q19 FP64, D3Q27 FP64, FP32.  Second rows: the
+// compressible model, for which 64 registers (FP32) or 128 between walls do
+// not hold what a node keeps.
 inline double march_least_gain(const MarchBox& b)
 {
-    static const double least[4][2][3] = {{{0.44, 0.44, 0.62}, {0.50, 0.50, 0.70}},
-                                          {{0.52, 0.60, 0.80}, {0.57, 0.64, 0.84}},
-                                          {{0.65, 0.65, 0.85}, {0.65, 0.65, 0.90}},
-                                          {{0.97, 1.08, 1.15}, {1.00, 1.15, 1.30}}};
+    static const double least[4][2][3] = {{{0.46, 0.46, 0.62}, {0.52, 0.58, 0.78}},
+                                          {{0.52, 0.60, 0.80}, {0.50, 0.60, 0.74}},
+                                          {{0.76, 0.70, 0.84}, {0.70, 0.72, 0.85}},
+                                          {{1.04, 1.16, 1.26}, {1.06, 1.26, 1.30}}};
     return least[march_wall_kind(b)][b.comp][b.storage_bytes == 4 ? 2 : b.lattice - 1];
 }
 
