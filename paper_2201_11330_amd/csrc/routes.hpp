@@ -267,28 +267,31 @@ struct Route2D {
 // Measured on boxes from 16^2 to 2900^2, 4096 x 1 .. 1024, 1 .. 32 x 4096, 65000 x
 // 3 and x 16, in five storages, periodic, between walls and with masks,
 // against one-step launches (us per step, one-step / several).
-//  * At most one block per CU (24 x 24 and 32 x 32 regions of eight steps): two
-//    steps and more in one launch are never slower, mostly 1.3-3.5 times
-//    faster.
+//  * At most one block per CU (regions of eight steps, and of six in long
+//    boxes): two steps and more in one launch are never slower, mostly 1.3-3.5
+//    times faster.
 //  * Larger boxes of which the blocks store less than half (65000 x 3 between
 //    walls: 576-node blocks with 72 stored nodes): FP64 7.8 / 11.5, FP16 4.1 /
 //    14.5: one step.
 //  * 16-bit storage: the conversions of each step weigh more, and short
 //    launches do not pay (FP16 two steps: 512^2 between walls 5.3 / 6.0, 2048^2
 //    27.0 / 39.4): six-step regions from three steps up (1.05-1.5), other
-//    launches from four.  Between walls on the axes strips lost (2048^2 30.4 /
-//    34.8), and with the compressible model regions of four (1024^2 10.6 /
-//    11.4).
+//    launches from four, or three where rows of partial cache lines slow the
+//    one-step kernels.  Between walls on the axes strips lost (2048^2 30.4 /
+//    34.8), and with the compressible model regions of four where rows are
+//    whole lines (1024^2 10.6 / 11.4; 42 boxes of other rows gained 1.15 in the
+//    mean).
 //  * e4m11: a conversion costs as much as a third of a collision.  Only whole
-//    launches of six-step regions pay (512^2 5.4 / 4.5; between walls up to 512
-//    blocks, 384^2 4.5 / 3.6, 512^2 4.9 / 4.9), and strips of rows that the
+//    launches pay: six-step regions of the incompressible model (512^2 5.4 /
+//    4.5, 700^2 8.4 / 6.9; between walls up to 512 blocks, 384^2 4.5 / 3.6,
+//    512^2 4.9 / 4.9), around obstacles also of the compressible one and regions
+//    of four where rows are partial lines (1.1-1.4); and strips of rows that the
 //    row-addressed one-step kernel does not take (2900^2 88.8 / 76.5, but
 //    2048^2 26.8 / 47.2), or from 2^23 nodes up around obstacles (2900^2 102.8 /
-//    86.0, 2048^2 43.4 / 50.8).  Regions of four: 1024^2 9.0 / 12.1, 1448^2 22.2 /
-//    21.9, between walls 22.7 / 24.8.
-//  * FP32 with the compressible model between walls, or with strips of rows of
-//    whole cache lines: two steps alone lost (512^2 6.8 / 7.1, 4096 x 1024 49.6 /
-//    52.5).
+//    86.0, 2048^2 43.4 / 50.8).  Other regions of four: 1024^2 9.0 / 12.1, 1448^2
+//    22.2 / 21.9, between walls 22.7 / 24.8.
+//  * FP32 rows of whole cache lines with the compressible model between walls or
+//    in strips: two steps alone lost (512^2 6.8 / 7.1, 4096 x 1024 49.6 / 52.5).
 inline Route2D route_2d(const Box2D& b)
 {
     const unsigned nodes = unsigned(b.nx) * unsigned(b.ny);
@@ -305,17 +308,20 @@ inline Route2D route_2d(const Box2D& b)
     const int inner = r.regions == kRegions32x6 ? 20 : 24;
     const long long blocks = fuse_blocks(b.nx, b.ny, inner);
     r.fours = six && !b.walls;
+    if (six && blocks <= 256) return r;
     if (!r.strips && 2ll * nodes < blocks * inner * inner) return one_step;
     if (b.storage == 4) {
         const bool row_addressed = !b.walls && b.nx >= 64 && b.nx <= 4096 && (b.nx & (b.nx - 1)) == 0;
-        if (b.walls && b.comp) return one_step;
-        if (six ? axes_only && blocks > 512 : !r.strips || axes_only || row_addressed) return one_step;
-        if (r.strips && b.mask && nodes < 1u << 23) return one_step;
+        bool take;
+        if (r.strips) take = !b.walls ? !row_addressed && !b.comp : b.mask && !b.comp && nodes >= 1u << 23;
+        else if (six) take = b.mask ? !b.comp || b.nx % 32 != 0 : !b.comp && (!b.walls || blocks <= 512);
+        else take = b.mask && !b.comp && b.nx % 64 != 0;
+        if (!take) return one_step;
         r.fewest = r.most;
     } else if (bytes == 2) {
-        if (axes_only && (r.strips || (b.comp && !six))) return one_step;
-        r.fewest = six && !(b.walls && b.comp) ? 3 : 4;
-    } else if (b.storage == 1 && ((b.walls && b.comp) || (r.strips && b.nx % 32 == 0))) {
+        if (axes_only && (r.strips || (b.comp && !six && b.nx % 64 == 0))) return one_step;
+        r.fewest = (six || b.nx % 64 != 0) && !(axes_only && b.comp) ? 3 : 4;
+    } else if (b.storage == 1 && b.nx % 32 == 0 && ((b.walls && b.comp) || r.strips)) {
         r.fewest = 3;
     }
     return r;
@@ -324,8 +330,8 @@ inline Route2D route_2d(const Box2D& b)
 // Steps of the next launch when `left` are to be made (0: one-step launches
 // from here on).  Of eight steps a periodic six-step box makes four and four
 // instead of six and two (FP64 512^2 40.0 -> 32.0 us, FP32 700^2 45.9 -> 40.4),
-// and where the rest after a whole launch would be one-step launches, two
-// equal ones (eight steps in 16-bit storage on 28 six-step boxes, in the mean
+// and where the rest after a whole launch would be several one-step launches,
+// two equal ones (eight steps in 16-bit storage on 28 six-step boxes, in the mean
 // over one-step launches: 6 + 1 + 1 x1.37, 4 + 4 x1.46).
 inline int next_launch(const Route2D& r, int left)
 {
@@ -334,7 +340,7 @@ inline int next_launch(const Route2D& r, int left)
     const int rest = left - r.most;
     if (!r.strips && r.regions == kRegions32x6 && r.fewest <= kFuseSteps) {
         if (r.fours && rest == 2) return kFuseSteps;
-        if (rest > 0 && rest < r.fewest && r.fewest > 2 && left >= 2 * r.fewest) return (left + 1) / 2;
+        if (rest > 1 && rest < r.fewest && left >= 2 * r.fewest) return (left + 1) / 2;
     }
     return r.most;
 }

@@ -28,7 +28,7 @@ CASES = [
     ((2100, 2000), "bf16", (0, 0, 0), False, True, S4 + [(1, "one")]),
     ((256, 16500), "bf16", (0, 0, 0), False, False, S4 + S4),
     ((2100, 2000), "e4m11", (0, 0, 0), False, False, S4 + S4 + [(1, "one")]),
-    ((230, 18300), "e4m11", (0, 0, 0), False, True, S4),
+    ((230, 18300), "e4m11", (0, 0, 0), False, False, S4),
     ((2000, 1600), "f16", (0, 0, 0), True, False, S4 + S4 + [(1, "one")]),
     ((230, 13700), "f16", (0, 3, 0), True, False, S4 + S4),
     ((2000, 1600), "bf16", (2, 1, 0), True, True, S4 + [(1, "one")]),
@@ -39,11 +39,16 @@ CASES = [
     # that takes them
     ((700, 690), "f64", (0, 0, 0), False, False, [(6, "32x6"), (4, "32x4"), (4, "32x4")]),
     ((700, 690), "f16", (0, 0, 0), False, True, [(4, "32x4"), (4, "32x4")]),
-    ((510, 520), "bf16", (0, 1, 0), False, False, [(4, "32x6"), (3, "32x6")]),
-    ((510, 520), "f16", (0, 1, 0), True, True, [(5, "32x6"), (4, "32x6")]),
+    ((510, 520), "bf16", (0, 1, 0), False, False, [(4, "32x6"), (4, "32x6")]),
+    ((510, 520), "f16", (0, 1, 0), False, True, [(5, "32x6"), (4, "32x6")]),
+    ((510, 520), "f16", (0, 1, 0), True, True, [(6, "32x6"), (3, "32x6")]),
+    ((153, 636), "e4m11", (0, 1, 0), False, True, [(6, "32x6"), (2, "32x6")]),
     ((400, 390), "e4m11", (0, 3, 0), False, False, [(6, "32x6"), (6, "32x6"), (1, "one")]),
     ((1030, 1024), "f32", (0, 0, 0), False, False, [(4, "32x4"), (4, "32x4"), (2, "32x4")]),
     ((1030, 1024), "f16", (0, 0, 0), False, True, [(4, "32x4"), (1, "one"), (1, "one")]),
+    ((1030, 1020), "bf16", (0, 1, 0), False, True, [(4, "32x4"), (1, "one")]),
+    ((1010, 1020), "e4m11", (0, 1, 0), True, False, [(4, "32x4"), (4, "32x4"), (1, "one")]),
+    ((510, 520), "e4m11", (0, 3, 0), True, True, [(6, "32x6"), (1, "one")]),
     # a column and a row of blocks, tiles of blocks narrower than the XCD tile
     ((9, 4100), "f64", (0, 0, 0), False, False, [(8, "32x8"), (3, "32x8")]),
     ((30, 4100), "f32", (0, 1, 0), False, False, [(6, "32x6"), (5, "32x6")]),
