@@ -179,10 +179,10 @@ lbm_status lbm_set_populations(lbm_ctx* ctx, const double* f);
 lbm_status lbm_get_populations(lbm_ctx* ctx, double* f);
 
 /*
- * Advances n >= 0 time steps.  Asynchronous on the bound stream.  A D2Q9
- * two-lattice box runs up to eight steps per launch; a large 3D two-lattice
- * box in FP64 or FP32 storage runs two steps per launch; the rest run one step
- * per launch.
+ * Advances n >= 0 time steps.  Asynchronous on the bound stream.  A launch
+ * makes up to eight steps of a D2Q9 two-lattice box and two of a large 3D
+ * two-lattice box in FP64 or FP32 storage, where that is faster for its size,
+ * storage, walls and model; elsewhere one step.
  * The state after any n is bit for bit that of n one-step launches.
  * Calls on a stream that the caller is capturing are recorded into the
  * caller's graph.  Replays continue from the state they find, also with other

@@ -24,7 +24,7 @@
 // 2 H))^2 of the useful collisions, less what the outer nodes leave out: each
 // step they skip as soon as nothing stored depends on them, whole wavefronts
 // at a time (128^2 FP64 1.38 -> 1.20 us per step, 256^2 1.79 -> 1.53, 512^2
-// around an obstacle 4.43 -> 4.37).  Which E and H: see fuse_regions().
+// around an obstacle 4.43 -> 4.37).  Which E and H: see route_2d().
 #pragma once
 
 #include "kernels.hpp"

@@ -10,7 +10,8 @@
 // 2", the second step) on the tile and stores it.  The work-items:
 //   * one wavefront per row of level 1 (rows 0 .. R - 1, stored rows
 //     1 .. R - 2), one lane per column, so a wavefront's loads and stores are
-//     64 consecutive nodes and a stored row starts on a cache line;
+//     64 consecutive nodes (which start on a cache line where nx is a multiple
+//     of 16 in FP64 or of 32 in FP32, and touch one line more elsewhere);
 //   * one wavefront for the two columns next to the tile (level 1 only).
 // Level 2 needs level 1 of plane q - 1 from three planes: e_z = -1 from
 // plane q, e_z = 0 from plane q - 1, e_z = +1 from plane q - 2.  Only the
@@ -21,10 +22,11 @@
 // them in registers.  The loads of plane q + 1 are issued before level 2 of
 // plane q - 1 and arrive while it runs.
 //
-// What bounds it: HBM.  A launch must read and write the state once for two
-// steps, half the bytes of the one-step kernels.  D3Q19 FP64 256^3 (rocprofv3
-// FETCH_SIZE and WRITE_SIZE, GB per launch): 2.79 read (2.55 stored, the
-// rest are the rings, mostly served by the L2 of the XCD), 2.55 written.
+// Which boxes take it: march_route().  What bounds it: HBM.  A launch must
+// read and write the state once for two steps, half the bytes of the one-step
+// kernels.  D3Q19 FP64 256^3 (rocprofv3 FETCH_SIZE and WRITE_SIZE, GB per
+// launch): 2.79 read (2.55 stored, the rest are the rings, mostly served by
+// the L2 of the XCD), 2.55 written.
 // Measured on one MI355X, us per step against the one-step kernels, periodic:
 // D3Q19 FP64 256^3 806 -> 467 (36,000 MLUPS), 512 x 128 x 128 405 -> 241,
 // 193 x 127 x 101 170 -> 117; FP32 256^3 407 -> 275; D3Q27 FP64 192^3
@@ -39,9 +41,11 @@
 // stays in registers.  Two rows per work-item (FP32: 64 x 28 tiles, one
 // workgroup per CU instead of two) ran 285 instead of 273 us per step at
 // 256^3, and issuing a quarter of the loads before level 1 was 10 % slower.
-// 16-bit storage does not take this path: its step is bound by the number
-// of vector memory instructions (84-87 % of the time the data path of the
-// L1 is busy), which this kernel does not reduce (FP16 256^3 197 -> 243 us).
+// 16-bit storage does not take this path: FP16 256^3 went from 197 to 243 us.
+// That form, held to the 64 registers of two workgroups per CU, issued 17.1 M
+// vector memory instructions per launch where the FP32 form issues 11.6 M
+// (LDS instructions: 11.59 M in both), for the same loads and stores of the
+// state; the rest is most likely registers spilled to memory.
 //
 // The arithmetic per node and step is that of the one-step kernels, in the
 // same order, so the state after two steps is bit for bit that of two
