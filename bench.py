@@ -451,7 +451,9 @@ def run_adjoint(n=128, steps=500, k=50, storage="f32", tau=0.7):
     (8 Fourier modes |K| <= 4, amplitude 0.02, seed 11), target from seed 12,
     J = 1/2 |u^N - u_tgt|^2.  Times the plain forward (lbm_step), the
     checkpointed forward (lbm_forward_record) and the backward sweep
-    (lbm_adjoint: segment recompute + adjoint steps + init map)."""
+    (lbm_adjoint: segment recompute + adjoint steps + init map).
+    bytes_model_ratio is that of one-step launches, (152 + 228) / 152 B per
+    node; the forward's two-step launches move half of its 152."""
     import torch
 
     from paper_2201_11330_amd import lbm

@@ -25,22 +25,28 @@
 // Which boxes take it: march_route().  What bounds it: HBM.  A launch must
 // read and write the state once for two steps, half the bytes of the one-step
 // kernels.  D3Q19 FP64 256^3 (rocprofv3 FETCH_SIZE and WRITE_SIZE, GB per
-// launch): 2.79 read (2.55 stored, the rest are the rings, mostly served by
-// the L2 of the XCD), 2.55 written.
+// launch): 2.83 read (2.55 stored, the rest are the rings, mostly served by
+// the L2 of the XCD), 2.55 written.  512 x 128 x 128 with a force between
+// walls moves 5.0 TB/s against these 5.8, with 1.6 times the vector
+// instructions per node.
 // Measured on one MI355X, us per step against the one-step kernels, periodic:
 // D3Q19 FP64 256^3 806 -> 467 (36,000 MLUPS), 512 x 128 x 128 405 -> 241,
 // 193 x 127 x 101 170 -> 117; FP32 256^3 407 -> 275; D3Q27 FP64 192^3
-// 498 -> 320.  512 x 128 x 128 between solid end planes: D3Q19 FP64
-// 405 -> 272, D3Q27 with a sphere in it 580 -> 410.
+// 498 -> 320.  512 x 128 x 128 with a force: D3Q19 FP64 between solid end
+// planes 405 -> 272, D3Q27 around a sphere 580 -> 415.
 //
 // Why this split: level 1 is made twice where tiles meet, (R / (R - 2)) x
 // (66 / 64) of the work, and the stored state is read (R + 2) / (R - 2)
 // times in y; 16 wavefronts are the most a workgroup can have, and 64 x 13
 // stored nodes per workgroup (64 x 9 for D3Q27 FP64, 12 wavefronts) the most
-// that LDS holds.  With 128 (168) registers everything a work-item keeps
-// stays in registers.  Two rows per work-item (FP32: 64 x 28 tiles, one
-// workgroup per CU instead of two) ran 285 instead of 273 us per step at
-// 256^3, and issuing a quarter of the loads before level 1 was 10 % slower.
+// that LDS holds.  Without walls everything a work-item keeps stays in its
+// 128 (D3Q27: 168, FP32: 64, 80) registers, but for two or three of the D3Q27
+// FP32 forms with a force.  With walls what walls above return waits in memory
+// (below), and up to 20 registers are spilled all the same (D3Q27 FP64
+// compressible with nodal walls; D3Q19 FP64 at most 6, FP32 at most 9).  Two
+// rows per work-item (FP32: 64 x 28 tiles, one workgroup per CU instead of
+// two) ran 285 instead of 273 us per step at 256^3, and issuing a quarter of
+// the loads before level 1 was 10 % slower.
 // 16-bit storage does not take this path: FP16 256^3 went from 197 to 243 us.
 // That form, held to the 64 registers of two workgroups per CU, issued 17.1 M
 // vector memory instructions per launch where the FP32 form issues 11.6 M
