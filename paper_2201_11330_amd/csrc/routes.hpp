@@ -290,6 +290,10 @@ struct Route2D {
 //    2048^2 26.8 / 47.2), or from 2^23 nodes up around obstacles (2900^2 102.8 /
 //    86.0, 2048^2 43.4 / 50.8).  Other regions of four: 1024^2 9.0 / 12.1, 1448^2
 //    22.2 / 21.9, between walls 22.7 / 24.8.
+//  * Regions of four that store less than three quarters (16 x 65000, 65000 x
+//    16): compressible between walls FP16 11.3 / 15.1 and FP32 two steps alone
+//    17.1 / 20.1; e4m11 around obstacles 14.5 / 17.4; the others 1.0-2.6 times
+//    faster.
 //  * FP32 rows of whole cache lines with the compressible model between walls or
 //    in strips: two steps alone lost (512^2 6.8 / 7.1, 4096 x 1024 49.6 / 52.5).
 inline Route2D route_2d(const Box2D& b)
@@ -310,18 +314,20 @@ inline Route2D route_2d(const Box2D& b)
     r.fours = six && !b.walls;
     if (six && blocks <= 256) return r;
     if (!r.strips && 2ll * nodes < blocks * inner * inner) return one_step;
+    const bool thin = !r.strips && !six && 4ll * nodes < 3ll * blocks * inner * inner;
     if (b.storage == 4) {
         const bool row_addressed = !b.walls && b.nx >= 64 && b.nx <= 4096 && (b.nx & (b.nx - 1)) == 0;
         bool take;
         if (r.strips) take = !b.walls ? !row_addressed && !b.comp : b.mask && !b.comp && nodes >= 1u << 23;
         else if (six) take = b.mask ? !b.comp || b.nx % 32 != 0 : !b.comp && (!b.walls || blocks <= 512);
-        else take = b.mask && !b.comp && b.nx % 64 != 0;
+        else take = b.mask && !b.comp && b.nx % 64 != 0 && !thin;
         if (!take) return one_step;
         r.fewest = r.most;
     } else if (bytes == 2) {
-        if (axes_only && (r.strips || (b.comp && !six && b.nx % 64 == 0))) return one_step;
+        if (axes_only && (r.strips || (b.comp && !six && (thin || b.nx % 64 == 0)))) return one_step;
         r.fewest = (six || b.nx % 64 != 0) && !(axes_only && b.comp) ? 3 : 4;
-    } else if (b.storage == 1 && b.nx % 32 == 0 && ((b.walls && b.comp) || r.strips)) {
+    } else if (b.storage == 1 && ((b.nx % 32 == 0 && ((b.walls && b.comp) || r.strips)) ||
+                                  (thin && axes_only && b.comp))) {
         r.fewest = 3;
     }
     return r;

@@ -72,6 +72,9 @@ def test_every_launch_makes_steps_that_its_kernel_can():
     ((1024, 1024), "e4m11", True, False, False, 48),   # 11.9, 13.4
     ((512, 512), "e4m11", False, False, False, 5),     # 4.6, 5.6
     ((512, 512), "f32", True, False, True, 2),
+    ((16, 65000), "f16", True, False, True, 48),       # 11.3, 15.1
+    ((16, 65000), "e4m11", True, True, False, 48),     # 14.5, 17.4
+    ((65000, 16), "f32", True, False, True, 2),        # 17.1, 20.1
 ], ids=str)
 def test_boxes_that_2d_launches_would_slow_down(q):
     assert all(kind == "one" for _, kind in routes.boxes_2d([q])[0])
